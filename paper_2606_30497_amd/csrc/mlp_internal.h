@@ -126,7 +126,7 @@ struct ReduceArgs {
 };
 
 size_t slot_stride_floats(int hidden);
-int tile_rows_per_wg(int64_t nb);
+int tile_workgroups(int hidden, int64_t nb);
 
 hipError_t launch_forward(const Ctx &c, const float *X, int64_t n_rows, const int32_t *idx,
                           int64_t B, float *ypred);
@@ -143,6 +143,7 @@ hipError_t hostloop_step(const Ctx &c, const float *X, int64_t n_rows, const flo
 
 // Persistent trainer
 bool plan_train(int hidden, int64_t batch, TrainPlan *plan);
+bool train_shape_forced();   // a test hook restricts the shape choice
 size_t persist_words_xch();
 size_t persist_words_rs(int hidden);
 size_t persist_words_ag(int hidden);

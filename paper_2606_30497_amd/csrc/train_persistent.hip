@@ -1238,6 +1238,8 @@ static const TrainPlan *all_plans(int *count) {
 //   MLP_REGULAR_LAUNCH=1   a regular launch instead of a cooperative one (the
 //                          same kernel and grid; for profiler runs, which end
 //                          with SIGSEGV after any cooperative launch).
+bool train_shape_forced() { return getenv("MLP_PX") != nullptr || getenv("MLP_INST") != nullptr; }
+
 bool plan_train(int hidden, int64_t batch, TrainPlan *plan) {
     const char *force = getenv("MLP_PX");
     const int fpx = force ? atoi(force) : 0;
