@@ -1192,7 +1192,11 @@ static TrainPlan plan_of(int inst) {
 }
 
 // The instantiated shapes: (index, groups PX, workgroups per group PR, rows per
-// workgroup R, units per group U). hidden = PX * U; batches up to PR * R.
+// workgroup R, units per group U). hidden = PX * U; batches up to PR * R. Every
+// width has shapes up to 4,096 rows (1024: 2,048, whose 128 units a group leave no
+// LDS or mask bits for 128 rows): a step of 1,000 rows at h = 64 takes 3.8 us here
+// and 6.9 us in the tile path's two launches, of 2,048 rows at h = 512 5.0 against
+// 12.1, of 4,096 at h = 32, the closest, 4.9 against 7.7.
 #define MLP_SHAPES(X)                                                   \
     X(0, 8, 32, 128, 32)   /* 32-256-1,  batch <= 4096 */             \
     X(1, 8, 32, 64, 32)    /* 32-256-1,  batch <= 2048 */             \
@@ -1209,7 +1213,20 @@ static TrainPlan plan_of(int inst) {
     X(12, 2, 16, 16, 128)  /* 32-256-1,  batch <= 256, two XCDs */    \
     X(13, 4, 4, 16, 64)    /* 32-256-1,  batch <= 64,  four XCDs */   \
     X(14, 8, 4, 32, 32)    /* 32-256-1,  batch <= 128 */              \
-    X(15, 8, 8, 32, 32)    /* 32-256-1,  batch <= 256 */
+    X(15, 8, 8, 32, 32)    /* 32-256-1,  batch <= 256 */              \
+    X(16, 8, 32, 32, 64)   /* 32-512-1,  batch <= 1024 */             \
+    X(17, 8, 32, 64, 64)   /* 32-512-1,  batch <= 2048 */             \
+    X(18, 8, 32, 128, 64)  /* 32-512-1,  batch <= 4096 */             \
+    X(19, 8, 32, 64, 128)  /* 32-1024-1, batch <= 2048 */             \
+    X(20, 4, 32, 32, 32)   /* 32-128-1,  batch <= 1024, four XCDs */  \
+    X(21, 4, 32, 64, 32)   /* 32-128-1,  batch <= 2048, four XCDs */  \
+    X(22, 4, 32, 128, 32)  /* 32-128-1,  batch <= 4096, four XCDs */  \
+    X(23, 2, 32, 32, 32)   /* 32-64-1,   batch <= 1024, two XCDs */   \
+    X(24, 2, 32, 64, 32)   /* 32-64-1,   batch <= 2048, two XCDs */   \
+    X(25, 2, 32, 128, 32)  /* 32-64-1,   batch <= 4096, two XCDs */   \
+    X(26, 1, 32, 32, 32)   /* 32-32-1,   batch <= 1024, one XCD */    \
+    X(27, 1, 32, 64, 32)   /* 32-32-1,   batch <= 2048, one XCD */    \
+    X(28, 1, 32, 128, 32)  /* 32-32-1,   batch <= 4096, one XCD */
 
 #define MLP_SHAPE_TYPE(I, PX, PR, R, U) typedef Shape<PX, PR, R, U> Shape##I;
 MLP_SHAPES(MLP_SHAPE_TYPE)

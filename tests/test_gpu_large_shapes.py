@@ -1,0 +1,43 @@
+"""The fused trainer's shapes for larger batches (up to 4,096 rows at every width up
+to 512 and 2,048 at h = 1024): gradients, training with a tail, and the exchange
+protocol's host model for their group counts."""
+import numpy as np
+import pytest
+
+import datagen
+import oracle
+from tests.parity import check
+from tests.test_exchange_protocol import violations
+from tests.test_gpu_parity import _check_grad, _ctx, _env, _train_gpu, mlp  # noqa: F401
+
+# (groups PX, workgroups per group PR, rows R, units U), from index 16 of the library's table
+LARGE_SHAPES = [(8, 32, 32, 64), (8, 32, 64, 64), (8, 32, 128, 64), (8, 32, 64, 128),
+                (4, 32, 32, 32), (4, 32, 64, 32), (4, 32, 128, 32),
+                (2, 32, 32, 32), (2, 32, 64, 32), (2, 32, 128, 32),
+                (1, 32, 32, 32), (1, 32, 64, 32), (1, 32, 128, 32)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", range(len(LARGE_SHAPES)))
+def test_large_shape(mlp, k):  # noqa: F811
+    px, pr, r, u = LARGE_SHAPES[k]
+    h, cap = px * u, pr * r
+    with _env(MLP_INST=16 + k):
+        d = datagen.make_data(64, h, seed=4, with_perm=False)
+        ctx, _, _ = _ctx(mlp, d.W1, d.W2, cap)
+        assert mlp.mlp_launch_info(ctx, cap, cap, 1) == (8 * pr, 1), "shape table out of step"
+        for B in (cap, cap // 2 + 3):
+            _check_grad(mlp, h, B, n=2 * cap, seed=k * 7 + B)
+        n, lr = 3 * cap - 5, 0.005
+        d = datagen.make_data(n, h, epochs=2, shuffle=True, seed=400 + k)
+        g1, g2, gsl, gel = _train_gpu(mlp, d, cap, lr, 2, perm=d.perm)
+    ref = oracle.train(d.X, d.Y, d.W1, d.W2, cap, lr, 2, perm=d.perm)
+    check("W1 - W1_0", g1 - d.W1, ref["W1"] - d.W1.astype(np.float64), 1e-3)
+    check("W2 - W2_0", g2 - d.W2, ref["W2"] - d.W2.astype(np.float64), 1e-3)
+    assert np.all(np.abs(gsl - ref["step_loss"]) <= 1e-3 * ref["step_loss"])
+    assert np.all(np.abs(gel - ref["epoch_loss"]) <= 1e-3 * ref["epoch_loss"])
+
+
+@pytest.mark.parametrize("px", [1, 2, 4])
+def test_exchange_protocol_of_32_workgroup_groups(px):
+    assert violations(px, 32, steps=4) == []
