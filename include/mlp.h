@@ -255,8 +255,10 @@ typedef struct mlp_deep_ctx *mlp_deep_t;
 int64_t mlp_deep_param_count(int32_t d_in, int32_t hidden, int32_t layers);
 
 /* Workspace bytes for batches up to max_batch (the activations of every layer
- * for max_batch rows, gradient partials, control words); 0 if unsupported.
- * The workspace must be 256-byte aligned. */
+ * for max_batch rows, gradient partials, control words; up to hidden 256 also
+ * the weights in matrix-core operand order); 0 if unsupported. The workspace
+ * must be 256-byte aligned. mlp_deep_init also takes one without that last
+ * part; calls then run as one launch per matrix product. */
 size_t mlp_deep_workspace_bytes(int32_t d_in, int32_t hidden, int32_t layers, int64_t max_batch);
 
 /* Create a context bound to caller-owned parameters (updated in place by

@@ -62,6 +62,7 @@
 #include <string.h>
 
 #include "bf16x3.h"
+#include "deep_internal.h"
 #include "lanes.h"
 #include "mlp.h"
 #include "mlp_internal.h"
@@ -75,7 +76,6 @@ constexpr int GSTAGES = 2;    // K chunks in flight (register stages; 3 or 4 mea
 constexpr int GEMM_CUS = 256; // compute units the tile choice plans for
 constexpr int SPLIT_MAX = 64; // row chunks of a weight-gradient product
 constexpr int OUT_CHUNKS_MAX = 256;   // row chunks of the output layer (dw_o partials)
-constexpr int DEEP_MAX_LAYERS = 8;
 
 enum { OP_NN = 0, OP_TN = 1, OP_NT = 2 };
 // Epilogues: none; ReLU (eq. 12); the ReLU mask of eq. 17; the mask and, from
@@ -90,21 +90,6 @@ template <int TM, int TN>
 struct Stage {
     float4 a[TM / 32], b[TN / 32];
 };
-
-// Sixteen zero bytes in device memory: a lane whose value lies outside its
-// operand loads these instead. The choice is made on the address, before the
-// load, and the loaded registers are not touched again until they are written
-// to LDS. (A load under a lane condition compiles to a branch and an immediate
-// wait for that load; a select of zero after the load is consumed, and so
-// waited for, wherever the scheduler places it, often among the MFMAs of an
-// earlier chunk. Either way the next chunks' loads stop overlapping the current
-// chunk's MFMAs.)
-__device__ __attribute__((aligned(16))) float g_zero16[4] = {0.f, 0.f, 0.f, 0.f};
-
-__device__ __forceinline__ float4 ld4(bool ok, const float *p) {
-    return *reinterpret_cast<const float4 *>(ok ? p : g_zero16);
-}
-__device__ __forceinline__ float ld1(bool ok, const float *p) { return *(ok ? p : g_zero16); }
 
 // ---- fp32 flavour: operands staged as fp32, v_mfma_f32_16x16x4f32 ----------
 //
@@ -536,32 +521,6 @@ __global__ __launch_bounds__(256, BF3 ? 3 : 1) void k_gemm_pair(const GemmArgs g
     }
 }
 
-// Xb[t][k] = X[r_t][k], Yb[t] = Y[r_t], r_t = idx[off + t] (or off + t);
-// out-of-range rows read row 0 and raise the sticky error.
-struct GatherArgs {
-    const float *X, *Y;
-    int64_t n_rows;
-    const int32_t *idx;
-    int64_t off, nb;
-    float *Xb, *Yb;
-    int32_t *err;
-};
-
-// Element e of the gather: float4 e % 8 of batch row e / 8.
-__device__ __forceinline__ void gather_one(const GatherArgs &g, int64_t e) {
-    if (e >= g.nb * (D_IN / 4)) return;
-    const int64_t t = e / (D_IN / 4);
-    const int q = (int)(e % (D_IN / 4));
-    int64_t r = g.idx ? (int64_t)g.idx[g.off + t] : g.off + t;
-    if (r < 0 || r >= g.n_rows) {
-        __hip_atomic_store(g.err, (int32_t)MLP_ERR_INDEX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        r = 0;
-    }
-    reinterpret_cast<float4 *>(g.Xb)[t * (D_IN / 4) + q] =
-        reinterpret_cast<const float4 *>(g.X)[r * (D_IN / 4) + q];
-    if (q == 0) g.Yb[t] = g.Y ? g.Y[r] : 0.0f;
-}
-
 __global__ __launch_bounds__(256) void k_deep_gather(const GatherArgs g) {
     gather_one(g, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
@@ -677,39 +636,7 @@ __global__ __launch_bounds__(256) void k_deep_apply(const float *__restrict__ pa
         return;
     }
     if ((int)blockIdx.x == napply) {
-        __shared__ float red[256];
-        const int i = threadIdx.x;
-        float v = 0.0f;
-        for (int64_t t0 = i; t0 < nb; t0 += 256 * U) {
-            float x[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const int64_t t = t0 + 256 * j;
-                x[j] = sq[t < nb ? t : nb - 1];
-            }
-#pragma unroll
-            for (int j = 0; j < U; ++j)
-                if (t0 + 256 * j < nb) v += x[j];
-        }
-        red[i] = v;
-        __syncthreads();
-        for (int w = 128; w >= 1; w >>= 1) {
-            if (i < w) red[i] += red[i + w];
-            __syncthreads();
-        }
-        if (i == 0) {
-            const float sse = red[0];
-            const float L = sse * ra.inv_nb;
-            flag_nonfinite(sse, &ra.ctl->err);
-            if (ra.loss) ra.loss[0] = L;
-            if (ra.step_loss) ra.step_loss[ra.step] = L;
-            if (ra.epoch_loss) {
-                double acc = ra.first_in_epoch ? 0.0 : ra.ctl->epoch_sse;
-                acc += (double)sse;
-                ra.ctl->epoch_sse = acc;
-                ra.epoch_loss[ra.epoch] = (float)(acc * ra.inv_n);
-            }
-        }
+        batch_loss(sq, nb, ra);
         return;
     }
     // Segment ends are multiples of 64, so a wave lies in one segment: look it
@@ -763,27 +690,6 @@ __global__ __launch_bounds__(256) void k_deep_apply(const float *__restrict__ pa
 // Host side
 // ---------------------------------------------------------------------------
 
-struct DeepCtx {
-    int hidden = 0, layers = 0;
-    int64_t max_batch = 0, np = 0;
-    float *params = nullptr;
-    Control *ctl = nullptr;
-    float *Xb = nullptr, *Yb = nullptr, *sq = nullptr;
-    float *H = nullptr;       // [layers][max_batch x hidden]
-    float *G[2] = {nullptr, nullptr};
-    float *part = nullptr;    // gradient partials, segment s at part_off[s] (plan of max_batch)
-    int64_t part_off[DEEP_MAX_LAYERS + 1] = {};
-    hipStream_t stream = nullptr;
-    bool profile = false, ev_valid = false;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-};
-
-static int64_t deep_np(int h, int L) { return (int64_t)D_IN * h + (int64_t)(L - 1) * h * h + h; }
-static int64_t layer_offset(int h, int l) {   // W_l, l = 1..L; w_o at l = L + 1
-    return l == 1 ? 0 : (int64_t)D_IN * h + (int64_t)(l - 2) * h * h;
-}
-static size_t pad64f(size_t n) { return (n + 63) / 64 * 64; }
-
 static bool deep_shape_ok(int32_t d_in, int32_t hidden, int32_t layers) {
     return d_in == D_IN && hidden >= 64 && hidden <= 1024 && hidden % 64 == 0 && layers >= 1 &&
            layers <= DEEP_MAX_LAYERS;
@@ -797,7 +703,7 @@ static bool deep_shape_ok(int32_t d_in, int32_t hidden, int32_t layers) {
 // gets one chunk per OUT_ROWS rows of the output kernel, at most OUT_CHUNKS_MAX. This
 // count never falls as nb grows, and the chunks a plan uses never exceed it, so
 // the count at max_batch sizes the partial buffer for every batch.
-static int64_t seg_chunks(int h, int L, int64_t nb, int s) {
+int64_t seg_chunks(int h, int L, int64_t nb, int s) {
     int64_t splits;
     if (s == 0 && L > 1) {
         // dW_1 comes from the epilogue of the back-propagation into layer 1,
@@ -857,6 +763,8 @@ static size_t deep_ws_floats(int h, int L, int64_t mb) {
     return pad64f(CTL_BYTES / 4) + pad64f(b * D_IN) + 2 * pad64f(b) +
            (size_t)(L + 2) * pad64f(b * (size_t)h) + (size_t)part_floats(h, L, mb);
 }
+
+static size_t deep_ws_bytes(int h, int L, int64_t mb) { return sizeof(float) * deep_ws_floats(h, L, mb); }
 
 // Tile choice: 64 x 64, or 32 x 64 where 64-row tiles would leave fewer than
 // two workgroups per CU (the 256-wide layers) or M itself is 32 (the weight
@@ -939,8 +847,6 @@ static hipError_t gemm_pair(hipStream_t st, const GemmArgs &g1, bool small1, con
         if (e_ != hipSuccess) return e_;   \
     } while (0)
 
-static unsigned blocks_of(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
-
 // Forward of nb gathered rows (Xb) through every hidden layer into c.H.
 static hipError_t deep_forward_layers(const DeepCtx &c, int64_t nb) {
     const int h = c.hidden;
@@ -994,10 +900,14 @@ static GatherArgs gather_args(const DeepCtx &c, const float *X, const float *Y, 
 // With gathered, the rows are already in Xb / Yb (gathered by the previous
 // step's update kernel); with next, the update kernel also gathers the rows of
 // the next step.
+// panel: on the panel path (panel_pays; one choice for all steps of a call, since a
+// step prepares the next one's weights and rows for its own path).
 static hipError_t deep_step(DeepCtx &c, const float *X, int64_t n_rows, const float *Y,
                             const int32_t *idx, int64_t off, int64_t nb, const ReduceArgs &ra,
-                            float *dparams, bool gathered = false, const GatherArgs *next = nullptr) {
+                            float *dparams, bool panel, bool gathered = false,
+                            const GatherArgs *next = nullptr) {
     const int h = c.hidden, L = c.layers;
+    if (panel) return panel_step(c, gather_args(c, X, Y, n_rows, idx, off, nb), nb, ra, dparams, gathered, next);
     const int64_t mbh = c.max_batch * h;
     if (!gathered) {
         hipLaunchKernelGGL(k_deep_gather, dim3(blocks_of(nb * (D_IN / 4), 256)), dim3(256), 0,
@@ -1074,7 +984,8 @@ extern "C" int64_t mlp_deep_param_count(int32_t d_in, int32_t hidden, int32_t la
 extern "C" size_t mlp_deep_workspace_bytes(int32_t d_in, int32_t hidden, int32_t layers,
                                            int64_t max_batch) {
     if (!deep_shape_ok(d_in, hidden, layers) || max_batch < 1 || max_batch > MLP_MAX_BATCH) return 0;
-    return sizeof(float) * deep_ws_floats(hidden, layers, max_batch);
+    return deep_ws_bytes(hidden, layers, max_batch) +
+           sizeof(float) * panel_ws_floats(hidden, layers, max_batch);
 }
 
 extern "C" mlp_status mlp_deep_init(mlp_deep_t *out, int32_t d_in, int32_t hidden, int32_t layers,
@@ -1083,9 +994,10 @@ extern "C" mlp_status mlp_deep_init(mlp_deep_t *out, int32_t d_in, int32_t hidde
     if (!out || !params || !workspace) return MLP_ERR_INVALID_ARG;
     if (!deep_shape_ok(d_in, hidden, layers) || d_out != 1) return MLP_ERR_UNSUPPORTED;
     if (max_batch < 1 || max_batch > MLP_MAX_BATCH) return MLP_ERR_INVALID_ARG;
-    if (ws_bytes < mlp_deep_workspace_bytes(d_in, hidden, layers, max_batch) ||
-        ((uintptr_t)workspace & 255u))
-        return MLP_ERR_WORKSPACE;
+    // a workspace without the panel path's part is taken too: the GEMM launches then
+    // serve every call
+    const size_t gemm_bytes = deep_ws_bytes(hidden, layers, max_batch);
+    if (ws_bytes < gemm_bytes || ((uintptr_t)workspace & 255u)) return MLP_ERR_WORKSPACE;
     mlp_deep_ctx *c = new (std::nothrow) mlp_deep_ctx();
     if (!c) return MLP_ERR_HIP;
     c->hidden = hidden;
@@ -1110,6 +1022,8 @@ extern "C" mlp_status mlp_deep_init(mlp_deep_t *out, int32_t d_in, int32_t hidde
     c->G[0] = take(bh);
     c->G[1] = take(bh);
     c->part = take((size_t)part_layout(hidden, layers, max_batch, c->part_off));
+    if (hidden <= PANEL_MAX_H && ws_bytes >= mlp_deep_workspace_bytes(d_in, hidden, layers, max_batch))
+        panel_carve(*c, (float *)((char *)workspace + gemm_bytes));
     Ctx tmp;
     tmp.ctl = c->ctl;
     tmp.stream = c->stream;
@@ -1135,6 +1049,7 @@ extern "C" mlp_status mlp_deep_forward(mlp_deep_t c, const float *X, int64_t n_r
     if (!c || !X || !Ypred || B < 1 || n_rows < 1) return MLP_ERR_INVALID_ARG;
     if (!idx && B > n_rows) return MLP_ERR_INVALID_ARG;
     const int h = c->hidden;
+    if (c->frag) return deep_status(panel_forward(*c, X, n_rows, idx, B, Ypred));
     const float *HL = c->H + (int64_t)(c->layers - 1) * c->max_batch * h;
     const float *wo = c->params + layer_offset(h, c->layers + 1);
     for (int64_t off = 0; off < B; off += c->max_batch) {
@@ -1167,7 +1082,7 @@ extern "C" mlp_status mlp_deep_backward(mlp_deep_t c, const float *X, int64_t n_
     ReduceArgs a = deep_args(c, B);
     a.sgd = 0;
     a.loss = loss;
-    return deep_status(deep_step(*c, X, n_rows, Y, idx, 0, B, a, dparams));
+    return deep_status(deep_step(*c, X, n_rows, Y, idx, 0, B, a, dparams, panel_pays(*c, B)));
 }
 
 static void deep_prof(mlp_deep_ctx *c, bool begin) {
@@ -1193,7 +1108,7 @@ extern "C" mlp_status mlp_deep_sgd_step(mlp_deep_t c, const float *X, int64_t n_
     a.lr = lr;
     a.loss = loss;
     deep_prof(c, true);
-    const mlp_status st = deep_status(deep_step(*c, X, n_rows, Y, idx, 0, B, a, nullptr));
+    const mlp_status st = deep_status(deep_step(*c, X, n_rows, Y, idx, 0, B, a, nullptr, panel_pays(*c, B)));
     deep_prof(c, false);
     return st;
 }
@@ -1213,6 +1128,7 @@ extern "C" mlp_status mlp_deep_train_epochs(mlp_deep_t c, const float *X, const 
     if (e != hipSuccess) return MLP_ERR_HIP;
     const int64_t spe = (n + batch - 1) / batch;
     const int64_t total = max_steps >= 0 && max_steps < spe * epochs ? max_steps : spe * epochs;
+    const bool panel = panel_pays(*c, batch);
     int64_t step = 0;
     deep_prof(c, true);
     for (int32_t ep = 0; ep < epochs && e == hipSuccess; ++ep) {
@@ -1240,7 +1156,7 @@ extern "C" mlp_status mlp_deep_train_epochs(mlp_deep_t c, const float *X, const 
                 nxt = gather_args(*c, X, Y, n, perm ? perm + (int64_t)ep2 * n : nullptr, off2,
                                   n - off2 < batch ? n - off2 : batch);
             }
-            e = deep_step(*c, X, n, Y, ix, off, nb, a, nullptr, step > 0, more ? &nxt : nullptr);
+            e = deep_step(*c, X, n, Y, ix, off, nb, a, nullptr, panel, step > 0, more ? &nxt : nullptr);
             if (e != hipSuccess) break;
             ++step;
         }

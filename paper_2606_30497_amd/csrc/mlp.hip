@@ -57,21 +57,6 @@ struct BatchItem {
     float ya, yb;
 };
 
-// The batch loss (eq. 14) from its sum of squared residuals, and the step and
-// epoch loss of a training call. One thread.
-__device__ __forceinline__ void record_loss(const ReduceArgs &a, float sse) {
-    const float L = sse * a.inv_nb;
-    flag_nonfinite(sse, &a.ctl->err);
-    if (a.loss) a.loss[0] = L;
-    if (a.step_loss) a.step_loss[a.step] = L;
-    if (a.epoch_loss) {
-        double acc = a.first_in_epoch ? 0.0 : a.ctl->epoch_sse;
-        acc += (double)sse;
-        a.ctl->epoch_sse = acc;
-        a.epoch_loss[a.epoch] = (float)(acc * a.inv_n);
-    }
-}
-
 // A step on nb rows (batch position t: row idx[off + t], or off + t). The products
 // are fp32 products on the bf16 matrix cores (bf16x3.h). Per pass of RB rows:
 //   forward   Z1 = X W1 from the split rows in LDS and the wave's split weights in

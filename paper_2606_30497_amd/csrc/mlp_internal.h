@@ -125,6 +125,21 @@ struct ReduceArgs {
     Control *ctl;
 };
 
+// The batch loss (eq. 14) from its sum of squared residuals, and the step and
+// epoch loss of a training call. One thread.
+__device__ __forceinline__ void record_loss(const ReduceArgs &a, float sse) {
+    const float L = sse * a.inv_nb;
+    flag_nonfinite(sse, &a.ctl->err);
+    if (a.loss) a.loss[0] = L;
+    if (a.step_loss) a.step_loss[a.step] = L;
+    if (a.epoch_loss) {
+        double acc = a.first_in_epoch ? 0.0 : a.ctl->epoch_sse;
+        acc += (double)sse;
+        a.ctl->epoch_sse = acc;
+        a.epoch_loss[a.epoch] = (float)(acc * a.inv_n);
+    }
+}
+
 size_t slot_stride_floats(int hidden);
 int tile_workgroups(int hidden, int64_t nb);
 

@@ -363,13 +363,16 @@ def mlp_deep_init(params: torch.Tensor, hidden: int, layers: int, max_batch: int
         raise MLPError("mlp_deep_workspace_bytes", -1)
     if workspace is None:
         workspace = torch.empty(need, dtype=torch.uint8, device=params.device)
-    _dev(workspace, "workspace", dtype=torch.uint8, numel=need)
+    _dev(workspace, "workspace", dtype=torch.uint8)
     if stream is None:
         stream = torch.cuda.current_stream(params.device).cuda_stream
     handle = _vp()
-    _check("mlp_deep_init", lib.mlp_deep_init(ctypes.byref(handle), D_IN, hidden, layers, 1,
-                                              max_batch, params.data_ptr(), workspace.data_ptr(),
-                                              workspace.numel(), stream))
+    # the library also takes a workspace without the part its panel path uses
+    status = lib.mlp_deep_init(ctypes.byref(handle), D_IN, hidden, layers, 1, max_batch,
+                               params.data_ptr(), workspace.data_ptr(), workspace.numel(), stream)
+    if status == -3 and workspace.numel() < need:
+        raise ValueError("workspace has %d elements, needs %d" % (workspace.numel(), need))
+    _check("mlp_deep_init", status)
     return DeepContext(handle, params, workspace, hidden, layers, max_batch)
 
 
