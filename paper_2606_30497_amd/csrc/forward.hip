@@ -213,8 +213,251 @@ static hipError_t launch_forward_h(const Ctx &c, const float *X, int64_t n_rows,
     return hipGetLastError();
 }
 
+// ---- many rows through 256 units or more ------------------------------------------
+//
+// A wave takes 128 units (four tiles of 32) and 32 rows a pass, as Z1^T: the weights
+// are the A operand of v_mfma_f32_32x32x16_bf16, the rows its B operand, so lane l
+// holds row l % 32 and, in its registers, units: ReLU, the W2 product and the sum
+// over the wave's units stay in the lane, and one half-wave exchange ends them. The
+// vector work of a pass (its epilogues and the next rows' splits, about five
+// instructions an MFMA) is issued between the MFMAs, one unit tile behind: on a bare
+// loop with constant operands 24 of these MFMAs and 160 vector instructions take 467
+// ns interleaved and 510 in two blocks, 48 16x16x32 ones 520 and 570.
+// Bound by the matrix cores' power: 10M rows through 256 units run at 220 TFLOP/s of
+// fp32 work, 1,320 of bf16, where a large library bf16 product reaches 1,150 on the
+// same card. Against k_forward, 4M rows: 256 units 341 -> 317 us, 512 642 -> 602, 1024
+// 1,303 -> 1,159.
+template <int H>
+struct WideShape {
+    static constexpr int UW = 128;                    // units per wave
+    static constexpr int NUT = UW / 32;               // unit tiles per wave
+    static constexpr int WPT = H / UW;                // waves per row tile
+    static constexpr int WAVES = WPT > 4 ? WPT : 4;   // waves per workgroup
+    static constexpr int TPI = WAVES / WPT;           // row tiles per workgroup pass
+    static constexpr int WAVES_PER_SIMD = 2;
+    static_assert(WPT * UW == H && WPT >= 2 && WPT <= 8, "shape");
+};
+
+template <int H, bool IDX>
+__global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_SIMD) void k_forward_wide(
+    const float *__restrict__ X, int64_t n_rows, const int32_t *__restrict__ idx, int64_t B,
+    const float *__restrict__ W1, const float *__restrict__ W2, float *__restrict__ ypred,
+    int32_t *err) {
+    using S = WideShape<H>;
+    constexpr int NUT = S::NUT, WPT = S::WPT, TPI = S::TPI;
+    __shared__ __attribute__((aligned(16))) float w2s[H];
+    __shared__ float part[2][S::WAVES][32];   // the waves' shares of a pass, by its parity
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 31, lh = lane >> 5;
+    const int wt = wave / WPT, wu = wave % WPT;
+
+    const int64_t ntiles = (B + 31) / 32;
+    const int64_t iters = (ntiles + TPI - 1) / TPI;
+    const int64_t stride = gridDim.x;
+    auto row0 = [&](int64_t i) { return (i * TPI + wt) * 32; };
+    // a pass's row of this lane; past the batch its last row, which is not stored
+    auto index_of = [&](int64_t i) -> int32_t {
+        const int64_t t = row0(i) + lr;
+        return IDX ? idx[t < B ? t : B - 1] : 0;
+    };
+    bool bad = false;   // an index out of range (its row reads row 0), raised at the end
+    // the row's inputs 8 lh .. + 7 at p[0..1], 16 + 8 lh .. + 7 at p[4..5]
+    auto row_at = [&](int64_t i, int32_t ix) {
+        const int64_t t = row0(i) + lr;
+        int64_t r = t < B ? t : B - 1;
+        if constexpr (IDX) {
+            const bool out = ix < 0 || ix >= n_rows;
+            bad |= out;
+            r = out ? 0 : ix;
+        }
+        return reinterpret_cast<const float4 *>(X + r * D_IN + 8 * lh);
+    };
+    constexpr int OFF[4] = {0, 1, 4, 5};
+
+    int64_t it = blockIdx.x;
+    float4 raw[4];
+    {
+        const float4 *p = row_at(it, index_of(it));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) raw[q] = p[OFF[q]];
+    }
+    int32_t ix = index_of(it + stride);
+    for (int j = threadIdx.x; j < H; j += 64 * S::WAVES) w2s[j] = W2[j];
+    // the wave's weights, for its whole life: unit wu UW + 32 u + lr, inputs
+    // 16 k + 8 lh .. + 7
+    u4v w[NUT][2][3];
+#pragma unroll
+    for (int u = 0; u < NUT; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float *c = W1 + (16 * k + 8 * lh) * H + wu * S::UW + 32 * u + lr;
+            uint32_t q[4][3];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) split_pair(c[2 * t * H], c[(2 * t + 1) * H], q[t]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) w[u][k][p] = u4v{q[0][p], q[1][p], q[2][p], q[3][p]};
+        }
+    // parts of the current rows: word t of part p of half k holds inputs 2 t, 2 t + 1
+    uint32_t xp[2][3][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float4 v = raw[2 * k + t / 2];
+            uint32_t q[3];
+            if (t % 2 == 0) split_pair(v.x, v.y, q);
+            else split_pair(v.z, v.w, q);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) xp[k][p][t] = q[p];
+        }
+    {
+        const float4 *p = row_at(it + stride, ix);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) raw[q] = p[OFF[q]];
+    }
+    ix = index_of(it + 2 * stride);
+    __syncthreads();   // w2s
+
+    // eqs. 12-13 of register j of unit tile c: the lane's unit 8 (j / 4) + 4 lh + j % 4,
+    // summed by j % 4. ReLU as an integer max on the bits: every negative float (-0
+    // included) has a negative pattern and becomes +0, every positive one stays; one
+    // instruction, where the float form costs two (a canonicalizing max first)
+    auto unit = [&](const f16v &c, int j, const float4 (&w2)[4], float (&y)[4]) __attribute__((always_inline)) {
+        const float4 q = w2[j / 4];
+        const float ws[4] = {q.x, q.y, q.z, q.w};
+        y[j % 4] = fmaf(__int_as_float(max(__float_as_int(c[j]), 0)), ws[j % 4], y[j % 4]);
+    };
+    auto load_w2 = [&](int u, float4 (&w2)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            w2[q] = *reinterpret_cast<const float4 *>(w2s + wu * S::UW + 32 * u + 8 * q + 4 * lh);
+    };
+    // a pass's outputs: the row's sum over the wave's units, then over the waves
+    auto finish = [&](int64_t i, int par, const float (&y)[4]) __attribute__((always_inline)) {
+        const int64_t r = row0(i) + lr;
+        const float s = xadd32((y[0] + y[1]) + (y[2] + y[3]));
+        if (lh == 0) part[par][wave][lr] = s;
+        __syncthreads();   // a wave is at most one pass ahead: the other parity's words
+        if (wu == 0 && lh == 0 && r >= 0 && r < B) {
+            float v = part[par][wt * WPT][lr];
+#pragma unroll
+            for (int q = 1; q < WPT; ++q) v += part[par][wt * WPT + q][lr];
+            ypred[r] = v;
+        }
+    };
+
+    // A value is computed where it stands: the compiler otherwise sinks what only the
+    // next pass uses past the end of this one, out of the MFMAs' shadow.
+    auto pin = [](auto &v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); };
+    // the previous pass's last unit tile and its sums so far (before the first pass,
+    // of rows below 0: not stored)
+    f16v prev = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float y[4] = {0.f, 0.f, 0.f, 0.f};
+    float4 w2[4];
+    load_w2(NUT - 1, w2);
+    int par = 0;
+    for (; it < iters; it += stride) {
+        const float4 *pn = row_at(it + 2 * stride, ix);   // the rows two passes on
+        ix = index_of(it + 3 * stride);
+        uint32_t nx[2][3][4];
+        float yn[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < NUT; ++u) {
+            constexpr int PX[6] = {2, 1, 0, 1, 0, 0}, PW[6] = {0, 1, 2, 0, 1, 0};
+            f16v c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            float ra = 0.f, rb = 0.f;   // what a split has left
+            // one MFMA and its share of the vector work at a time: Z1 of unit tile u (eq. 11,
+            // the six part products smallest first); two registers of the tile before it a
+            // slot; then the splits of the next rows
+#pragma unroll
+            for (int s = 0; s < 12; ++s) {
+                const int q = s / 2, k = s % 2;
+                c = mfma_bf16_32(w[u][k][PW[q]],
+                                 u4v{xp[k][PX[q]][0], xp[k][PX[q]][1], xp[k][PX[q]][2], xp[k][PX[q]][3]}, c);
+                if (s < 8) {
+                    float(&ys)[4] = u == 0 ? y : yn;
+                    unit(prev, 2 * s, w2, ys);
+                    unit(prev, 2 * s + 1, w2, ys);
+                    pin(ys[(2 * s) % 4]);
+                    pin(ys[(2 * s + 1) % 4]);
+                } else {   // a pair in two slots
+                    const int pr = 2 * u + (s - 8) / 2, kk = pr / 4, t = pr % 4;
+                    const float4 v = raw[pr / 2];
+                    if (s % 2 == 0) {
+                        ra = pr % 2 == 0 ? v.x : v.z;
+                        rb = pr % 2 == 0 ? v.y : v.w;
+                        nx[kk][0][t] = bf16_pair(ra, rb);
+                        ra -= __uint_as_float(nx[kk][0][t] << 16);
+                        rb -= __uint_as_float(nx[kk][0][t] & 0xFFFF0000u);
+                        pin(ra);
+                        pin(rb);
+                    } else {
+                        nx[kk][1][t] = bf16_pair(ra, rb);
+                        ra -= __uint_as_float(nx[kk][1][t] << 16);
+                        rb -= __uint_as_float(nx[kk][1][t] & 0xFFFF0000u);
+                        nx[kk][2][t] = bf16_pair(ra, rb);
+                        pin(nx[kk][1][t]);
+                        pin(nx[kk][2][t]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // the inputs just split are free: the rows two passes on
+            raw[u] = pn[OFF[u]];
+            load_w2(u, w2);
+            prev = c;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        finish(it - stride, par, y);
+        par ^= 1;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[v] = yn[v];
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) xp[k][p][t] = nx[k][p][t];
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) unit(prev, j, w2, y);
+    finish(it - stride, par, y);
+    if (IDX && bad)
+        __hip_atomic_store(err, (int32_t)MLP_ERR_INDEX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int H>
+static hipError_t launch_forward_wide(const Ctx &c, const float *X, int64_t n_rows,
+                                      const int32_t *idx, int64_t B, float *ypred) {
+    using S = WideShape<H>;
+    const int64_t iters = ((B + 31) / 32 + S::TPI - 1) / S::TPI;
+    const int64_t cap = (int64_t)S::WAVES_PER_SIMD * 4 / S::WAVES * (c.num_cu > 0 ? c.num_cu : 256);
+    const int grid = (int)(iters < cap ? iters : cap);
+    if (idx)
+        hipLaunchKernelGGL((k_forward_wide<H, true>), dim3(grid), dim3(64 * S::WAVES), 0, c.stream, X, n_rows,
+                           idx, B, c.W1, c.W2, ypred, &c.ctl->err);
+    else
+        hipLaunchKernelGGL((k_forward_wide<H, false>), dim3(grid), dim3(64 * S::WAVES), 0, c.stream, X, n_rows,
+                           idx, B, c.W1, c.W2, ypred, &c.ctl->err);
+    return hipGetLastError();
+}
+
+// Fewer rows leave k_forward_wide's longer passes a few waves (1,777 rows through 1024
+// units: 5.4 us here, 6.7 there; 20,000 rows 11.0 and 10.7, 256 units 6.9 and 6.4), and
+// at 64 and 128 units it is no faster (4M rows through 128: 183 and 188).
+constexpr int64_t WIDE_ROWS = 16384;
+
 hipError_t launch_forward(const Ctx &c, const float *X, int64_t n_rows, const int32_t *idx,
                           int64_t B, float *ypred) {
+    if (B >= WIDE_ROWS) {
+        switch (c.hidden) {
+        case 256: return launch_forward_wide<256>(c, X, n_rows, idx, B, ypred);
+        case 512: return launch_forward_wide<512>(c, X, n_rows, idx, B, ypred);
+        case 1024: return launch_forward_wide<1024>(c, X, n_rows, idx, B, ypred);
+        }
+    }
     switch (c.hidden) {
     case 32: return launch_forward_h<32>(c, X, n_rows, idx, B, ypred);
     case 64: return launch_forward_h<64>(c, X, n_rows, idx, B, ypred);

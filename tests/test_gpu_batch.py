@@ -3,8 +3,11 @@ the edges of its passes: 32-row passes (64 at h = 32), one workgroup up to 64 ro
 and more passes than workgroups (256) from 8,193 rows (16,385 at h = 32)."""
 import numpy as np
 import pytest
+import torch
 
 import datagen
+import oracle
+from tests.parity import rel
 from tests.test_gpu_parity import _check_grad, _ctx, _rows, _to, mlp  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +40,28 @@ def test_step_applies_the_gradient(mlp, h, B):  # noqa: F811
     u = 2.0 ** -24
     assert bool(((w1 - e1).abs() <= 4 * u * (e1.abs() + lr * dW1.abs())).all())
     assert bool(((w2 - e2).abs() <= 4 * u * (e2.abs() + lr * dW2.abs())).all())
+
+
+@pytest.mark.parametrize("h", [256, 512, 1024])
+@pytest.mark.parametrize("B", [16383, 16384, 16385, 70001])
+@pytest.mark.parametrize("gather", [True, False])
+def test_forward_of_many_rows(mlp, h, B, gather):  # noqa: F811
+    """The forward pass around the row count from which the wider nets take 32-row
+    passes, and over several passes a wave with a ragged last one; outputs past B
+    stay untouched and an index out of range is flagged."""
+    n = 3000 if gather else B
+    d = datagen.make_data(n, h, seed=h, with_perm=False)
+    ctx, _, _ = _ctx(mlp, d.W1, d.W2, 64)
+    idx = _rows(np.random.default_rng(B), n, B) if gather else None
+    out = torch.full((B + 40,), 7.0, device="cuda")
+    mlp.mlp_forward(ctx, _to(d.X), None if idx is None else _to(idx), B=B, out=out)
+    mlp.mlp_check_errors(ctx)
+    got = out.cpu().numpy()
+    assert rel(got[:B], oracle.forward(d.X, d.W1, d.W2, idx=idx)) < 1e-5
+    assert np.all(got[B:] == 7.0)
+    if gather:
+        idx[B // 2] = n
+        mlp.mlp_forward(ctx, _to(d.X), _to(idx), B=B, out=out)
+        with pytest.raises(mlp.MLPError) as e:
+            mlp.mlp_check_errors(ctx)
+        assert e.value.status == -6
