@@ -104,6 +104,19 @@ struct Shape {
     static constexpr int RSW = 32 * U;                     // exchange-B words per workgroup
     static constexpr int GBW = (PR * RSW + PR + 31) / 32 * 32;   // exchange-B words per group
     static constexpr int RPL = R / (8 * NLW);              // rows per loader lane
+    // Sleep (64 clocks each) before the first poll of exchange A. us a step, without
+    // and with: 32-256-1 at 4,096 rows 4.77 / 4.53 (two row tiles: the second's
+    // forward already covers part of it; 4.69 with 5), at 2,048 4.29 / 3.70 and at 256
+    // 3.10 / 3.01, 32-1024-1 at 1,024 5.32 / 5.11, 32-64-1 at 1,000 3.85 / 3.53. One
+    // group has no exchange A, but the loaders take the pause (32-32-1 at 256: 2.42 /
+    // 2.31).
+    static constexpr int A_DELAY = PX == 1 || RTW == 2 ? 2 : 5;
+    // The same before the owners' first poll of exchange B and everyone's of C (inside
+    // an XCD a round trip is shorter): with both 32-256-1 at 256 rows 3.02 / 2.92,
+    // 32-32-1 at 256 2.31 / 2.22, 32-512-1 at 2,048 4.55 / 4.49, 32-1024-1 at 1,024
+    // 5.07 / 5.01; with two row tiles the owners are late enough already.
+    static constexpr int B_DELAY = RTW == 2 ? 0 : 4;
+    static constexpr int C_DELAY = 4;
     // LDS carve-up, in bytes
     static constexpr int B_XR = 0;                               // [2][3][R][XRS] bf16: staged rows, split
     static constexpr int B_WP = B_XR + 2 * 3 * R * XRS * 2;      // [3][U][WPS] bf16: W1 slice, split
@@ -667,6 +680,10 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
                 const int hh = li >> 3;
                 const int peer = (li & 7) % PX;
                 W2 wa[RTW];
+                // The first poll is timed to sample just after the words land: a poll
+                // that leaves at once comes back stale and costs the wait its round
+                // trip of about 0.6 us.
+                __builtin_amdgcn_s_sleep(S::A_DELAY);
                 if constexpr (PX > 1) {
 #pragma unroll
                     for (int i = 0; i < RTW; ++i)
@@ -713,12 +730,14 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
                     const int ra = tile * 16 + 4 * lq + 2 * hh;   // first row of the lane's pair
                     float y0 = 0.f, y1 = 0.f;
                     if constexpr (PX > 1) {
-                        W2 one[1] = {wa[i]};
-                        wt.settle<1>(one, tag, [&](int) {
-                            return ld2(rA, bA + 8u * (uint32_t)(peer * RMAX + ra));
-                        });
-                        y0 = val_of(one[0].a);
-                        y1 = val_of(one[0].b);
+                        // both row tiles' words at once: after a wait for tile 0 alone
+                        // a stale word of tile 1 costs another round trip
+                        if (i == 0)
+                            wt.settle<1>(wa, tag, [&](int q) {
+                                return ld2(rA, bA + 8u * (uint32_t)(peer * RMAX + (wr * RTW + q) * 16 + 4 * lq + 2 * hh));
+                            });
+                        y0 = val_of(wa[i].a);
+                        y1 = val_of(wa[i].b);
                         if (i == 0) PHASE(3); else PHASE(4);
                         if constexpr (PX == 8) {
                             y0 += dppf<0x141>(y0);   // row_half_mirror: lanes i, 7 - i
@@ -863,6 +882,7 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
                 ct[8] = ct[7];
                 ct[9] = ct[7];
                 if (owner) {
+                    __builtin_amdgcn_s_sleep(S::B_DELAY);
                     // words (k0, k0 + 1) of unit jl from sources sg * LPS + b, in source order
                     // (in chunks of at most 8 sources, to bound registers)
                     constexpr int CHB = LPS < 8 ? LPS : 8;
@@ -929,6 +949,7 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
                     if (a.mode == 0) __syncthreads();
                 PHASE(10);
                 if (a.mode == 0) {
+                    __builtin_amdgcn_s_sleep(S::C_DELAY);
                     // the W1 parts in chunks of CHC word pairs per thread (to bound
                     // registers); the W2 words (threads below U / 2) load first
                     const uint32_t cbase = 8u * (uint32_t)((par * PX + gx) * S::CW);
