@@ -34,7 +34,8 @@
 // GEMM tile: 64 x 64 (or 32 x 64, 32 x 32) outputs per workgroup of four waves
 // (each a quarter, as 16 x 16 MFMA tiles), K in chunks of 32 staged in LDS,
 // alternating between two LDS buffers (one barrier per chunk); the next two
-// chunks' global loads are in flight while the current chunk is computed. Two
+// chunks' global loads are in flight while the current chunk is computed. Large
+// products of h >= 384 take 128 x 128 tiles of their own (gemm_block128). Two
 // flavours of the product:
 // - fp32: v_mfma_f32_16x16x4f32 on fp32 operands (in LDS, operands read along
 //   m or n stored k-major with a row stride of TM + 16 floats, operands read
@@ -275,28 +276,46 @@ __host__ __device__ constexpr int gemm_lds_floats(int TM, int TN, bool bf3) {
     return 2 * (tile_floats(TM, bf3) + tile_floats(TN, bf3));
 }
 
+// Where a wave's accumulators lie in its TM/2 x TN/2 quarter of the tile: register v of
+// its f4 (i, j) is row row(i) + v, column col(j). 16 x 16 MFMA tiles, or (128 x 128
+// tiles) 32 x 32 ones, four f4 down a tile.
+template <int TM, int TN>
+struct AccLayout {
+    static constexpr bool W32 = TM == 128;
+    static constexpr int NI = W32 ? TM / 16 : TM / 32, NJ = W32 ? TN / 64 : TN / 32;
+    int r, c;
+    __device__ __forceinline__ AccLayout() {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        r = (wave >> 1) * (TM / 2) + 4 * (W32 ? lane >> 5 : lane >> 4);
+        c = (wave & 1) * (TN / 2) + (lane & (W32 ? 31 : 15));
+    }
+    __device__ __forceinline__ int row(int i) const { return r + (W32 ? 8 : 16) * i; }
+    __device__ __forceinline__ int col(int j) const { return c + (W32 ? 32 : 16) * j; }
+};
+
 // The MASK_DW1 epilogue's second half: the workgroup's tile of G_1 (rows
 // [m0, m0 + TM) of the batch, units [n0, n0 + TN); masked, in g, rows past M
 // zero) times the same rows of X gives that row tile's partial of
 // dW_1 = X^T G_1 (eq. 18 at the first layer) for those units, a sum over the
 // tile's TM rows in a fixed order. Both operands go through LDS (the K loop is
 // done with it); the product is TM / 4 steps of v_mfma_f32_16x16x4f32 per 16 x 16
-// output tile, two output tiles per wave (D_IN = 32 inputs x TN = 64 units).
+// output tile, TN / 32 output tiles per wave (D_IN = 32 inputs x TN units).
 template <int TM, int TN, int MI, int NJ>
 __device__ __forceinline__ void dw1_partial(const GemmArgs &g, int bx, int by, const f4 (&gt)[MI][NJ],
                                             float *__restrict__ lds) {
-    static_assert(TN == 64 && D_IN == 32, "dW_1 partial tile");
+    const AccLayout<TM, TN> at;
+    static_assert(D_IN == 32, "dW_1 partial tile");
+    constexpr int NU = TN / 32;   // unit tiles of a wave
     constexpr int XS = D_IN + 1, GS = TN + 1;   // LDS row strides (floats)
     float *Xs = lds, *Gs = lds + TM * XS;
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
     const int li = lane & 15, lq = lane >> 4;
-    const int wm = wave >> 1, wn = wave & 1;
     const int64_t m0 = (int64_t)bx * TM;
     __syncthreads();   // every wave is done with the K loop's LDS
 #pragma unroll
-    for (int e = t; e < TM * D_IN; e += 256) {
-        const int r = e / D_IN, k = e % D_IN;
+    for (int q = 0; q < TM * D_IN / 256; ++q) {
+        const int e = t + 256 * q, r = e / D_IN, k = e % D_IN;
         const int64_t m = m0 + r;
         Xs[r * XS + k] = m < g.M ? g.X[m * D_IN + k] : 0.0f;
     }
@@ -306,26 +325,82 @@ __device__ __forceinline__ void dw1_partial(const GemmArgs &g, int bx, int by, c
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                Gs[(wm * (TM / 2) + i * 16 + 4 * lq + v) * GS + wn * (TN / 2) + j * 16 + li] = gt[i][j][v];
+                Gs[(at.row(i) + v) * GS + at.col(j)] = gt[i][j][v];
     __syncthreads();
-    // wave w: inputs 16 (w & 1) .. + 15, units 32 (w >> 1) .. + 31 (two tiles)
-    const int it = wave & 1, ub = (wave >> 1) * 32;
-    f4 p[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+    // wave w: inputs 16 (w & 1) .. + 15, half w >> 1 of the units
+    const int it = wave & 1, ub = (wave >> 1) * (TN / 2);
+    f4 p[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) p[u] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < TM / 4; ++ks) {
         const int r = 4 * ks + lq;
         const float a = Xs[r * XS + 16 * it + li];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < NU; ++u)
             p[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Gs[r * GS + ub + 16 * u + li], p[u], 0, 0, 0);
     }
     // lane (li, lq) holds P[input 16 it + 4 lq + v][unit ub + 16 u + li]
     float *dst = g.dw1 + (int64_t)bx * g.dw1_split + (int64_t)by * TN;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < NU; ++u)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             dst[(int64_t)(16 * it + 4 * lq + v) * g.N + ub + 16 * u + li] = p[u][v];
+}
+
+// The mask operand of a MASK epilogue, in the layout of the accumulators (clamped
+// addresses, no lane condition).
+template <int TM, int TN, int NI, int NJ>
+__device__ __forceinline__ void load_mask(const GemmArgs &g, int bx, int by, float (&gm)[NI][NJ][4]) {
+    const AccLayout<TM, TN> at;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int n = by * TN + at.col(j);
+            const int nc = n < g.N ? n : g.N - 1;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t m = (int64_t)bx * TM + at.row(i) + v;
+                gm[i][j][v] = g.G[(m < g.M ? m : g.M - 1) * g.ldg + nc];
+            }
+        }
+}
+
+// The epilogue of one output tile, acc (plus lo in the bf16x3 flavour).
+template <int EP, int TM, int TN, bool BF3, int NI, int NJ, int GI, int GJ>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int bx, int by, int bz,
+                                              f4 (&acc)[NI][NJ], const f4 (&lo)[NI][NJ],
+                                              const float (&gm)[GI][GJ][4], float *__restrict__ lds) {
+    static_assert(NI == AccLayout<TM, TN>::NI && NJ == AccLayout<TM, TN>::NJ, "layout");
+    const AccLayout<TM, TN> at;
+    constexpr bool MASKED = EP == EP_MASK || EP == EP_MASK_DW1;
+    const int64_t m0 = (int64_t)bx * TM, M = g.M;
+    const int n0 = by * TN, N = g.N, ldc = g.ldc;
+    float *Cz = g.C + (int64_t)bz * g.c_split;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int n = n0 + at.col(j);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t m = m0 + at.row(i) + v;
+                if (m >= M || n >= N) {
+                    if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = 0.0f;   // no row: no term
+                    continue;
+                }
+                float r = BF3 ? acc[i][j][v] + lo[i][j][v] : acc[i][j][v];
+                // eq. 12; a NaN passes (a diverged step must reach the loss: an
+                // infinite operand leaves NaN in its split parts)
+                if constexpr (EP == EP_RELU) r = r <= 0.0f ? 0.0f : r;
+                if constexpr (MASKED) r = gm[i][j][v] > 0.0f ? r : 0.0f;    // eq. 17
+                if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = r;
+                Cz[m * ldc + n] = r;
+            }
+        }
+    if constexpr (EP == EP_MASK_DW1) dw1_partial<TM, TN, NI, NJ>(g, bx, by, acc, lds);
 }
 
 // One output tile (bx, by) of split bz; lds holds gemm_lds_floats(TM, TN, BF3).
@@ -338,8 +413,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &g, int bx, int by, in
     float *Bs2[2] = {lds + 2 * tile_floats(TM, BF3), lds + 2 * tile_floats(TM, BF3) + tile_floats(TN, BF3)};
     const float *__restrict__ A = g.A;
     const float *__restrict__ B = g.B;
-    const float *__restrict__ G = g.G;
-    const int lda = g.lda, ldb = g.ldb, ldg = g.ldg, ldc = g.ldc, N = g.N;
+    const int lda = g.lda, ldb = g.ldb, N = g.N;
     const int64_t M = g.M, K = g.K, kc = g.kc;
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
@@ -376,20 +450,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &g, int bx, int by, in
     // so that its loads overlap the K loop instead of each waiting at the end
     constexpr bool MASKED = EP == EP_MASK || EP == EP_MASK_DW1;
     float gm[MASKED ? MI : 1][MASKED ? NJ : 1][4];
-    if constexpr (MASKED) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int n = n0 + wn * (TN / 2) + j * 16 + li;
-                const int nc = n < N ? n : N - 1;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int64_t m = m0 + wm * (TM / 2) + i * 16 + 4 * lq + v;
-                    gm[i][j][v] = G[(m < M ? m : M - 1) * ldg + nc];
-                }
-            }
-    }
+    if constexpr (MASKED) load_mask<TM, TN>(g, bx, by, gm);
     // fp32: eight k steps of 4 on the matrix cores.
     // bf16x3: lane (li, lq) reads k in [8 lq, 8 lq + 8) of row li of each 16-row
     // operand tile, for every part. The leading part product a0 b0 accumulates
@@ -470,30 +531,220 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &g, int bx, int by, in
             mfma_chunk(buf);
         }
     }
-    // ---- epilogue: lane holds C[4 lq + v][li] of each 16 x 16 tile ----
-    float *Cz = g.C + (int64_t)bz * g.c_split;
+    gemm_epilogue<EP, TM, TN, BF3>(g, bx, by, bz, acc, lo, gm, lds);
+}
+
+// ---- 128 x 128 tiles -----------------------------------------------------------
+//
+// The bf16x3 product on 128 x 128 output tiles, a 64 x 64 quarter a wave. At 64 x 64
+// the LDS bounds it: a chunk's operand reads and writes take 576 clocks of a CU's LDS
+// against 384 of its matrix cores; here 1,152 against 1,536. One workgroup fills a CU
+// (96 KB of LDS, a wave a SIMD), so nothing else hides the operands' split: chunk
+// c + 1 is split and written to the other LDS buffer between the MFMAs of chunk c, and
+// chunk c + 2 loaded meanwhile; a wave issues an instruction every 5-6 clocks, so the
+// MFMAs are the 32 x 32 x 16 ones, half as many instructions (16 x 16 x 32: 182 us a
+// step). Three LDS buffers, a chunk's first operands read before its barrier: 191-195 us
+// (register moves). Each chunk's operand is a buffer that ends at its last row, so
+// loads need no lane conditions and their offsets never change. 32-1024x2-1 at 4,096
+// rows: 208.8 -> 173.1 us a step.
+constexpr int BT = 128;
+constexpr int BT_LDS = 2 * 2 * bf3_tile_floats(BT) * 4;   // bytes
+constexpr int BT_K_MIN = 256;                             // shortest K they are used for
+
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+
+// Thread t's 16 values of an operand tile of 128 x and 32 k:
+//   k-major: x = 2 (t % 64) + 0..1, k = 8 (t / 64) + 0..7 (8-byte loads along x);
+//   x-major: x = t / 8 + 32 h, k = 4 (t % 8) + 0..3, h < 4 (16-byte loads along k).
+template <bool KMAJOR>
+struct Operand128 {
+    const float *P;
+    int64_t ke;
+    int ld, rows;       // x-major: rows of the tile inside the matrix
+    uint32_t at[KMAJOR ? 8 : 4];
+    float v[2][16];
+    __device__ __forceinline__ void init(const float *p, int ld_, int64_t xlim, int64_t x0, int64_t ke_, int t) {
+        ld = ld_;
+        ke = ke_;
+        P = p + (KMAJOR ? x0 : x0 * ld);
+        rows = xlim - x0 < BT ? (int)(xlim - x0) : BT;
+        if constexpr (KMAJOR) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+            for (int j = 0; j < 8; ++j) at[j] = 4u * (uint32_t)((8 * (t >> 6) + j) * ld + 2 * (t & 63));
+        } else {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int n = n0 + wn * (TN / 2) + j * 16 + li;
+            for (int h = 0; h < 4; ++h) at[h] = 4u * (uint32_t)(((t >> 3) + 32 * h) * ld + 4 * (t & 7));
+        }
+    }
+    // chunk k0 .. k0 + 31 into register set q; past ke nothing is read (zeros)
+    __device__ __forceinline__ void fetch(int q, int64_t k0) {
+        const float *base = P + (KMAJOR ? k0 * ld : k0);
+        int words = 0;
+        if (k0 < ke) {
+            if constexpr (KMAJOR) words = (int)(ke - k0 < GK ? ke - k0 : GK) * ld - (ld - BT);
+            else words = rows * ld - (ld - GK);
+        }
+        const rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), (short)0, 4 * words, 0x00020000);
+        if constexpr (KMAJOR) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t m = m0 + wm * (TM / 2) + i * 16 + 4 * lq + v;
-                if (m >= M || n >= N) {
-                    if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = 0.0f;   // no row: no term
-                    continue;
-                }
-                float r = BF3 ? acc[i][j][v] + lo[i][j][v] : acc[i][j][v];
-                // eq. 12; a NaN passes (a diverged step must reach the loss: an
-                // infinite operand leaves NaN in its split parts)
-                if constexpr (EP == EP_RELU) r = r <= 0.0f ? 0.0f : r;
-                if constexpr (MASKED) r = gm[i][j][v] > 0.0f ? r : 0.0f;    // eq. 17
-                if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = r;
-                Cz[m * ldc + n] = r;
+            for (int j = 0; j < 8; ++j) {
+                const u2v x = __builtin_amdgcn_raw_buffer_load_b64(r, at[j], 0, 0);
+                v[q][2 * j] = __uint_as_float(x[0]);
+                v[q][2 * j + 1] = __uint_as_float(x[1]);
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const u4v x = __builtin_amdgcn_raw_buffer_load_b128(r, at[h], 0, 0);
+#pragma unroll
+                for (int n = 0; n < 4; ++n) v[q][4 * h + n] = __uint_as_float(x[n]);
             }
         }
-    if constexpr (EP == EP_MASK_DW1) dw1_partial<TM, TN, MI, NJ>(g, bx, by, acc, lds);
+    }
+    // half hf of set q, split, to the LDS tile S ([part][x][k], granules as swz places them)
+    __device__ __forceinline__ void stash(int q, int hf, uint16_t *S, int t) const {
+        if constexpr (KMAJOR) {
+            const int x = 2 * (t & 63) + hf, kr = 8 * (t >> 6);
+            uint32_t w[4][3];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) split_pair(v[q][4 * j + hf], v[q][4 * j + 2 + hf], w[j]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                *reinterpret_cast<u4v *>(S + (p * BT + x) * GK + swz(x, kr)) = u4v{w[0][p], w[1][p], w[2][p], w[3][p]};
+        } else {
+#pragma unroll
+            for (int h = 2 * hf; h < 2 * hf + 2; ++h) {
+                const int x = (t >> 3) + 32 * h, kr = 4 * (t & 7);
+                uint32_t w[2][3];
+                split_pair(v[q][4 * h], v[q][4 * h + 1], w[0]);
+                split_pair(v[q][4 * h + 2], v[q][4 * h + 3], w[1]);
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    *reinterpret_cast<u2v *>(S + (p * BT + x) * GK + swz(x, kr)) = u2v{w[0][p], w[1][p]};
+            }
+        }
+    }
+};
+
+template <int OP, int EP>
+__device__ __forceinline__ void gemm_block128(const GemmArgs &g, int bx, int by, int bz, float *__restrict__ lds) {
+    constexpr int TW = bf3_tile_floats(BT);
+    uint16_t *As2[2] = {reinterpret_cast<uint16_t *>(lds), reinterpret_cast<uint16_t *>(lds + TW)};
+    uint16_t *Bs2[2] = {reinterpret_cast<uint16_t *>(lds + 2 * TW), reinterpret_cast<uint16_t *>(lds + 3 * TW)};
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = t >> 6;
+    const int lr = lane & 31, lh = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int64_t m0 = (int64_t)bx * BT, M = g.M;
+    const int n0 = by * BT;
+    const int64_t kb = (int64_t)bz * g.kc;
+    const int64_t ke = kb + g.kc < g.K ? kb + g.kc : g.K;
+    const int64_t nch = (ke - kb + GK - 1) / GK;
+
+    Operand128<OP == OP_TN> a;
+    Operand128<OP != OP_NT> b;
+    a.init(g.A, g.lda, M, m0, ke, t);
+    b.init(g.B, g.ldb, g.N, n0, ke, t);
+    a.fetch(0, kb);
+    b.fetch(0, kb);
+    a.fetch(1, kb + GK);
+    b.fetch(1, kb + GK);
+    f16v acc[2][2], lo[2][2];   // 32 x 32 MFMA tiles
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = lo[i][j][v] = 0.f;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+        a.stash(0, hf, As2[0], t);
+        b.stash(0, hf, Bs2[0], t);
+    }
+    // chunk c (LDS buffer and register set q = c & 1): the barrier ends every wave's
+    // writes of it and its reads of chunk c - 1, whose buffer chunk c + 1 then takes
+    auto chunk = [&](int64_t c, int q) __attribute__((always_inline)) {
+        __syncthreads();
+        a.fetch(q, kb + (c + 2) * GK);
+        b.fetch(q, kb + (c + 2) * GK);
+        const uint16_t *As = As2[q], *Bs = Bs2[q];
+        // k half kk of the chunk: parts of the A tiles and of the B tiles
+        u4v ap[2][2][3], bp[2][2][3];
+        auto load = [&](int kk) __attribute__((always_inline)) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    const int k = swz(lr, 16 * kk + 8 * lh);
+                    bp[kk][x][p] = *reinterpret_cast<const u4v *>(Bs + (p * BT + wn * 64 + x * 32 + lr) * GK + k);
+                    ap[kk][x][p] = *reinterpret_cast<const u4v *>(As + (p * BT + wm * 64 + x * 32 + lr) * GK + k);
+                }
+        };
+        load(0);
+        constexpr int PA[5] = {2, 1, 0, 1, 0}, PB[5] = {0, 1, 2, 0, 1};
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if (kk == 0 && i == 0) load(1);
+                if (kk == 0) a.stash(q ^ 1, i, As2[q ^ 1], t);
+                else b.stash(q ^ 1, i, Bs2[q ^ 1], t);
+#pragma unroll
+                for (int p = 0; p < 5; ++p)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) lo[i][j] = mfma_bf16_32(ap[kk][i][PA[p]], bp[kk][j][PB[p]], lo[i][j]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16_32(ap[kk][i][0], bp[kk][j][0], acc[i][j]);
+                // four vector instructions of the split after each MFMA (176.9 us a step at
+                // 32-1024x2-1 and 4,096 rows as the compiler orders them, 179.2 with three,
+                // 173.1 with four, 174.6 with five)
+#pragma unroll
+                for (int e = 0; e < 12; ++e) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    int64_t c = 0;
+    for (; c + 2 <= nch; c += 2) {
+        chunk(c, 0);
+        chunk(c + 1, 1);
+    }
+    if (c < nch) chunk(c, 0);
+    constexpr bool MASKED = EP == EP_MASK || EP == EP_MASK_DW1;
+    f4 r[8][2], rl[8][2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                r[i][j][v] = acc[i / 4][j][4 * (i % 4) + v];
+                rl[i][j][v] = lo[i / 4][j][4 * (i % 4) + v];
+            }
+    float gm[MASKED ? 8 : 1][MASKED ? 2 : 1][4];
+    if constexpr (MASKED) load_mask<BT, BT>(g, bx, by, gm);
+    gemm_epilogue<EP, BT, BT, true>(g, bx, by, bz, r, rl, gm, lds);
+}
+
+template <int OP, int EP>
+__global__ __launch_bounds__(256, 1) void k_gemm128(const GemmArgs g) {
+    extern __shared__ __attribute__((aligned(16))) float lds128[];
+    gemm_block128<OP, EP>(g, blockIdx.x, blockIdx.y, blockIdx.z, lds128);
+}
+
+template <int OP1, int EP1, int OP2, int EP2>
+__global__ __launch_bounds__(256, 1) void k_gemm_pair128(const GemmArgs g1, const GemmArgs g2) {
+    extern __shared__ __attribute__((aligned(16))) float lds128[];
+    const int n1 = g1.gx * g1.gy * g1.gz;
+    int b = blockIdx.x;
+    if (b < n1) {
+        gemm_block128<OP1, EP1>(g1, b % g1.gx, (b / g1.gx) % g1.gy, b / (g1.gx * g1.gy), lds128);
+    } else {
+        b -= n1;
+        gemm_block128<OP2, EP2>(g2, b % g2.gx, (b / g2.gx) % g2.gy, b / (g2.gx * g2.gy), lds128);
+    }
 }
 
 // The bf16x3 tiles are compiled for three workgroups per CU (the most their LDS
@@ -769,9 +1020,7 @@ static size_t deep_ws_bytes(int h, int L, int64_t mb) { return sizeof(float) * d
 // Tile choice: 64 x 64, or 32 x 64 where 64-row tiles would leave fewer than
 // two workgroups per CU (the 256-wide layers) or M itself is 32 (the weight
 // gradient of W_1); a single product (not a pair) narrows that to 32 x 32 where
-// it would still leave fewer than four. Larger tiles (128 x 64, 128 x 128) halve the operand
-// traffic per MFMA but leave one or two workgroups per CU on the 1024-wide
-// products, which measured 6-8 % slower than four. The 64 x 64 tiles (the
+// it would still leave fewer than four. The 64 x 64 tiles (the
 // MFMA-heavy products of wide layers) run the bf16x3 flavour, the narrower
 // ones (latency-bound, few chunks each) the fp32 one: bf16x3 made the 1024-wide
 // net 8 % faster and the 256-wide ones 3-6 % slower.
@@ -804,6 +1053,51 @@ static GemmArgs gemm_args(const float *A, int lda, const float *B, int ldb, floa
     return g;
 }
 
+// The product on 128 x 128 tiles.
+static GemmArgs tiles128(GemmArgs g) {
+    g.gx = (int)((g.M + BT - 1) / BT);
+    g.gy = g.N / BT;
+    return g;
+}
+// Whether a launch takes 128 x 128 tiles, one workgroup a CU: where they keep the CUs
+// busy and K is long enough to pay for the prologue. Busy: all tiles' K over the CUs,
+// against the K of the CU that finishes last when tiles go out in order to whichever is
+// free. A single product from three quarters of it (1,536 tiles' K of 2,048 at
+// 32-1024x2-1 and 3,072 rows: 60,000 rows forward 1,293 -> 1,180 us; 32-768x2-1 at
+// 4,096 878 -> 818), a pair from seven eighths (32-512x2-1 at 6,500 rows, 0.80: 111.6 us
+// a step with the pair on 64 x 64 tiles, 114.5 on these; 32-1024x2-1 at 2,048, 1.0:
+// 119.5 -> 106.4).
+static bool long_tiles(const GemmArgs &g) {
+    return g.N % BT == 0 && g.M >= BT && (g.kc < g.K ? g.kc : g.K) >= BT_K_MIN;
+}
+static bool fits128(const GemmArgs &g) {
+    const GemmArgs t = tiles128(g);
+    const int64_t n = (int64_t)t.gx * t.gy * t.gz, rounds = (n + GEMM_CUS - 1) / GEMM_CUS;
+    return long_tiles(g) && 4 * n >= 3 * rounds * GEMM_CUS;
+}
+static bool pair_fits128(const GemmArgs &g1, const GemmArgs &g2) {
+    if (!long_tiles(g1) || !long_tiles(g2)) return false;
+    const GemmArgs t1 = tiles128(g1), t2 = tiles128(g2);
+    const int64_t n1 = (int64_t)t1.gx * t1.gy * t1.gz, n2 = (int64_t)t2.gx * t2.gy * t2.gz;
+    const int64_t k1 = g1.kc < g1.K ? g1.kc : g1.K, k2 = g2.kc < g2.K ? g2.kc : g2.K;
+    // after the first product's tiles r CUs are done at a + k1, the others at a
+    const int64_t r = n1 % GEMM_CUS, a = n1 / GEMM_CUS * k1;
+    auto room = [&](int64_t t) {   // the second's tiles done by t
+        return (GEMM_CUS - r) * ((t - a) / k2) + r * (t > a + k1 ? (t - a - k1) / k2 : 0);
+    };
+    int64_t x = n2 / GEMM_CUS, y = 0;
+    while (room(a + x * k2) < n2) ++x;
+    if (x > 0 && r > 0 && a + x * k2 > a + k1) {
+        y = (a + x * k2 - a - k1) / k2;   // the last end of a CU of the other kind before that
+        if (room(a + k1 + y * k2) < n2) y = -1;
+    } else {
+        y = -1;
+    }
+    int64_t end = y >= 0 ? a + k1 + y * k2 : a + x * k2;
+    if (r > 0 && end < a + k1) end = a + k1;
+    return 8 * (n1 * k1 + n2 * k2) >= 7 * end * GEMM_CUS;
+}
+
 template <int OP, int EP>
 static hipError_t gemm(hipStream_t st, const float *A, int lda, const float *B, int ldb, float *C,
                        int ldc, int64_t c_split, int64_t M, int N, int64_t K, int splits,
@@ -811,7 +1105,11 @@ static hipError_t gemm(hipStream_t st, const float *A, int lda, const float *B, 
     bool small;
     const GemmArgs g = gemm_args(A, lda, B, ldb, C, ldc, c_split, M, N, K, splits, kc, G, ldg, &small);
     const dim3 grid((unsigned)g.gx, (unsigned)g.gy, (unsigned)g.gz);
-    if (small && (int64_t)g.gx * g.gy * g.gz < 4 * GEMM_CUS) {
+    if (fits128(g)) {
+        const GemmArgs w = tiles128(g);
+        hipLaunchKernelGGL((k_gemm128<OP, EP>), dim3((unsigned)w.gx, (unsigned)w.gy, (unsigned)w.gz), dim3(256),
+                           BT_LDS, st, w);
+    } else if (small && (int64_t)g.gx * g.gy * g.gz < 4 * GEMM_CUS) {
         // 32 x 32 tiles where 32 x 64 ones would leave fewer than four
         // workgroups per CU
         GemmArgs gn = g;
@@ -829,6 +1127,13 @@ static hipError_t gemm(hipStream_t st, const float *A, int lda, const float *B, 
 template <int OP1, int EP1, int OP2, int EP2>
 static hipError_t gemm_pair(hipStream_t st, const GemmArgs &g1, bool small1, const GemmArgs &g2,
                             bool small2) {
+    if (pair_fits128(g1, g2)) {
+        const GemmArgs w1 = tiles128(g1), w2 = tiles128(g2);
+        hipLaunchKernelGGL((k_gemm_pair128<OP1, EP1, OP2, EP2>),
+                           dim3((unsigned)(w1.gx * w1.gy * w1.gz + w2.gx * w2.gy * w2.gz)), dim3(256), BT_LDS, st,
+                           w1, w2);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)(g1.gx * g1.gy * g1.gz + g2.gx * g2.gy * g2.gz));
     if (small1 && small2)
         hipLaunchKernelGGL((k_gemm_pair<OP1, EP1, 32, GT, OP2, EP2, 32, GT, false>), grid, dim3(256), 0, st, g1, g2);
@@ -918,33 +1223,36 @@ static hipError_t deep_step(DeepCtx &c, const float *X, int64_t n_rows, const fl
     const float *HL = c.H + (int64_t)(L - 1) * mbh;
     const float *wo = c.params + layer_offset(h, L + 1);
     int cur = 0;
-    // with more than one layer, dW_1 comes from the epilogue of the
-    // back-propagation into layer 1 (one partial per row tile of that product)
-    int dw1_rows = 0;
-    if (L > 1) {
-        bool small;
-        (void)gemm_args(c.G[0], h, c.params, h, c.G[1], h, 0, nb, h, h, 1, h, c.Xb, h, &small);
-        dw1_rows = small ? 32 : GT;
-    }
     SplitPlan sp;
-    split_plan(h, L, nb, c.part_off, dw1_rows, &sp);
+    split_plan(h, L, nb, c.part_off, GT, &sp);
+    // the products of layer l's weight gradient dW_l = H_{l-1}^T G_l (eq. 18, split over
+    // row chunks) and of G_{l-1} = (G_l W_l^T) (.) [H_{l-1} > 0] (eq. 17 one layer down)
+    auto input = [&](int l) { return l == 1 ? c.Xb : c.H + (int64_t)(l - 2) * mbh; };
+    auto wgrad_args = [&](int l, bool *small) {
+        const int K = l == 1 ? D_IN : h;
+        return gemm_args(input(l), K, c.G[cur], h, c.part + sp.part_off[l - 1], h, (int64_t)K * h, K, h, nb,
+                         sp.splits[l - 1], sp.kc[l - 1], nullptr, 0, small);
+    };
+    auto back_args = [&](int l, bool *small) {
+        return gemm_args(c.G[cur], h, c.params + layer_offset(h, l), h, c.G[cur ^ 1], h, 0, nb, h, h, 1, h,
+                         input(l), h, small);
+    };
+    if (L > 1) {
+        // dW_1 comes from the epilogue of the back-propagation into layer 1, one
+        // partial per row tile of that product
+        bool s1, s2;
+        const GemmArgs gw = wgrad_args(2, &s1), gg = back_args(2, &s2);
+        split_plan(h, L, nb, c.part_off, pair_fits128(gw, gg) ? BT : s2 ? 32 : GT, &sp);
+    }
     // output layer: r^2, G_L and the dw_o partials of each row chunk
     DEEP_TRY(launch_out(c, HL, wo, nb, sp.kc[L], sp.splits[L], c.part + sp.part_off[L]));
     for (int l = L; l >= 1; --l) {
-        const int K = l == 1 ? D_IN : h;
-        const float *Hin = l == 1 ? c.Xb : c.H + (int64_t)(l - 2) * mbh;
-        // dW_l = H_{l-1}^T G_l, eq. 18, split over row chunks
         bool s1, s2;
-        const GemmArgs gw = gemm_args(Hin, K, c.G[cur], h, c.part + sp.part_off[l - 1], h,
-                                      (int64_t)K * h, K, h, nb, sp.splits[l - 1], sp.kc[l - 1],
-                                      nullptr, 0, &s1);
+        const GemmArgs gw = wgrad_args(l, &s1);
         if (l > 1) {
-            // G_{l-1} = (G_l W_l^T) (.) [H_{l-1} > 0], eq. 17 one layer down; it
-            // reads G_l as the weight gradient does and writes the other buffer,
-            // so the two products share one launch. Into layer 1 (l = 2) its
-            // epilogue also forms the row tile's partial of dW_1 = X^T G_1.
-            GemmArgs gg = gemm_args(c.G[cur], h, c.params + layer_offset(h, l), h, c.G[cur ^ 1], h,
-                                    0, nb, h, h, 1, h, Hin, h, &s2);
+            // the back-propagation reads G_l as the weight gradient does and writes the
+            // other buffer, so the two products share one launch
+            GemmArgs gg = back_args(l, &s2);
             if (l == 2) {
                 gg.X = c.Xb;
                 gg.dw1 = c.part + sp.part_off[0];
@@ -955,8 +1263,8 @@ static hipError_t deep_step(DeepCtx &c, const float *X, int64_t n_rows, const fl
             }
             cur ^= 1;
         } else if (L == 1) {
-            DEEP_TRY((gemm<OP_TN, EP_NONE>(c.stream, Hin, K, c.G[cur], h, c.part + sp.part_off[l - 1], h,
-                                           (int64_t)K * h, K, h, nb, sp.splits[l - 1], sp.kc[l - 1])));
+            DEEP_TRY((gemm<OP_TN, EP_NONE>(c.stream, input(l), D_IN, c.G[cur], h, c.part + sp.part_off[l - 1], h,
+                                           (int64_t)D_IN * h, D_IN, h, nb, sp.splits[l - 1], sp.kc[l - 1])));
         }
     }
     // every gradient's partials summed and applied; the last workgroup takes the loss
