@@ -1253,15 +1253,12 @@ static TrainPlan plan_of(int inst) {
 MLP_SHAPES(MLP_SHAPE_TYPE)
 #undef MLP_SHAPE_TYPE
 
+// Filled once, before the first reader: contexts plan on threads of their own.
 static const TrainPlan *all_plans(int *count) {
-    static TrainPlan plans[32];
-    static int n = 0;
-    if (n == 0) {
-#define MLP_SHAPE_PLAN(I, PX, PR, R, U) plans[n++] = plan_of<Shape##I>(I);
-        MLP_SHAPES(MLP_SHAPE_PLAN)
+#define MLP_SHAPE_PLAN(I, PX, PR, R, U) plan_of<Shape##I>(I),
+    static const TrainPlan plans[] = {MLP_SHAPES(MLP_SHAPE_PLAN)};
 #undef MLP_SHAPE_PLAN
-    }
-    *count = n;
+    *count = (int)(sizeof(plans) / sizeof(plans[0]));
     return plans;
 }
 
