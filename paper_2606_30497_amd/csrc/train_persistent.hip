@@ -1309,6 +1309,15 @@ size_t persist_words_rs(int hidden) { return (size_t)2 * 32 * ((size_t)hidden * 
 // two parities x (three bf16-part words per W1 pair of inputs, one W2 word) per unit
 size_t persist_words_ag(int hidden) { return (size_t)2 * hidden * 49; }
 
+static bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &s) != hipSuccess) {
+        (void)hipGetLastError();   // the launch reports what is wrong with the stream
+        return false;
+    }
+    return s == hipStreamCaptureStatusActive;
+}
+
 hipError_t launch_train(Ctx &c, TrainArgs &a) {
     a.xch = c.xch;
     a.rs = c.rs;
@@ -1325,7 +1334,11 @@ hipError_t launch_train(Ctx &c, TrainArgs &a) {
     // tags of the next call start past every tag this call can use; a range
     // that would leave 32 bits restarts at 1 over cleared exchange words
     const TagPlan tp = plan_tags(c.tag_base, a.steps);
-    if (tp.clear) {
+    // A captured launch runs with the same tags at every replay: its words are cleared
+    // before it (of an earlier replay's) and after it (of tags that a launch outside
+    // the graph may reach again once the tags have wrapped).
+    const bool captured = is_capturing(c.stream);
+    if (tp.clear || captured) {
         const hipError_t e = clear_words(c, c.xch, c.xch_words);
         if (e != hipSuccess) return e;
     }
@@ -1333,13 +1346,15 @@ hipError_t launch_train(Ctx &c, TrainArgs &a) {
     c.tag_base = tp.next;
     const char *rl = getenv("MLP_REGULAR_LAUNCH");
     const bool regular = rl && rl[0] == '1' && c.num_cu >= a.plan.grid;
+    hipError_t e = hipErrorInvalidValue;
     switch (a.plan.inst) {
 #define MLP_SHAPE_CASE(I, PX, PR, R, U) \
-    case I: return launch_shape<Shape##I>(c.stream, a, regular);
+    case I: e = launch_shape<Shape##I>(c.stream, a, regular); break;
         MLP_SHAPES(MLP_SHAPE_CASE)
 #undef MLP_SHAPE_CASE
     }
-    return hipErrorInvalidValue;
+    if (e == hipSuccess && captured) e = clear_words(c, c.xch, c.xch_words);
+    return e;
 }
 
 }  // namespace mlp
