@@ -76,6 +76,7 @@ struct TrainArgs {
     int32_t *err;
     uint32_t tag_base;        // tags of this call: tag_base + step
     uint64_t timeout_ticks;   // per-wait limit in s_memrealtime ticks (100 MHz)
+    uint64_t start_ticks;     // the start barrier's
     int32_t force_coherent;   // 1: device-coherent stores even when placement checks out
     uint64_t *phase;          // nullable: per-phase cycle sums of every workgroup
     TrainPlan plan;

@@ -422,6 +422,141 @@ constexpr int PHASE_FROM = 8, PHASE_WORDS = 16;
     } while (0)
 
 // ---------------------------------------------------------------------------
+// A launch whose workgroups were not all resident in time
+// ---------------------------------------------------------------------------
+
+// Bit of the start barrier's count (reg[9]): the launch was given up.
+constexpr int START_GIVEN_UP = 1 << 30;
+
+// The whole call by one workgroup: where other work on the GPU keeps some of the
+// launch's workgroups from starting within the limit, the last of them to leave
+// trains alone. No other workgroup has touched the weights. Plain fp32, and few
+// registers rather than speed (it shares the kernel with the step loop): per batch the
+// residuals of all rows, a wave a row, into LDS (batches the trainer takes have at
+// most 4,096 rows); then a thread a unit sums the unit's gradient over the rows and
+// updates its column of W1, which no other unit's gradient reads.
+template <int H>
+__device__ __forceinline__ void train_alone(float *lds) {
+    constexpr int RG = 64, NW = NTHR / 64;
+    float *xs = lds, *ys = xs + RG * D_IN, *red = ys + RG, *res = red + NW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float *W1 = COLD(W1), *W2 = COLD(W2);
+    const int64_t n = COLD(n), batch = COLD(batch), steps = COLD(steps);
+    const int64_t spe = (n + batch - 1) / batch;
+    double epoch_sse = 0.0;
+    int64_t e = 0, sb = 0;
+#pragma unroll 1
+    for (int64_t s = 0; s < steps; ++s) {
+        const int64_t off = sb * batch;
+        const int nb = (int)(n - off < batch ? n - off : batch);
+        // rows t0 .. t0 + RG - 1 of the batch (those it has) into LDS
+        auto stage = [&](int t0) {
+            const int rows = nb - t0 < RG ? nb - t0 : RG;
+            const int32_t *perm = COLD(perm);
+            const int64_t n_rows = COLD(n_rows);
+            const float *X = COLD(X), *Y = COLD(Y);
+            __syncthreads();   // the rows before them were read
+#pragma unroll 1
+            for (int i = tid; i < rows * (D_IN + 1); i += NTHR) {
+                const int r = i / (D_IN + 1), k = i % (D_IN + 1);
+                const int64_t t = off + t0 + r;
+                int64_t row = perm ? (int64_t)perm[e * n + t] : t;
+                if (row < 0 || row >= n_rows) {
+                    __hip_atomic_store(COLD(err), (int32_t)MLP_ERR_INDEX, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                    row = 0;
+                }
+                if (k < D_IN) xs[r * D_IN + k] = X[row * D_IN + k];
+                else ys[r] = Y[row];
+            }
+            __syncthreads();
+            return rows;
+        };
+#pragma unroll 1
+        for (int t0 = 0; t0 < nb; t0 += RG) {
+            const int rows = stage(t0);
+#pragma unroll 1
+            for (int r = wave; r < rows; r += NW) {
+                float yp = 0.0f;
+#pragma unroll 1
+                for (int j = lane; j < H; j += 64) {
+                    float z = 0.0f;
+#pragma unroll 8
+                    for (int k = 0; k < D_IN; ++k) z = fmaf(xs[r * D_IN + k], W1[k * H + j], z);   // eq. 11
+                    yp = fmaf(z > 0.0f ? z : 0.0f, W2[j], yp);                                      // eqs. 12-13
+                }
+                yp = sum64(yp);
+                if (lane == 0) res[t0 + r] = yp - ys[r];
+            }
+        }
+        __syncthreads();
+        float sse = 0.0f;
+#pragma unroll 1
+        for (int t = tid; t < nb; t += NTHR) sse = fmaf(res[t], res[t], sse);   // eq. 14
+        sse = sum64(sse);
+        if (lane == 0) red[wave] = sse;
+        const float scale = 2.0f / (float)nb;
+#pragma unroll 1
+        for (int j0 = 0; j0 < H; j0 += NTHR) {
+            const int j = j0 + tid < H ? j0 + tid : H - 1;
+            float w1[D_IN], p[D_IN], q = 0.0f;
+            const float w2 = W2[j];
+#pragma unroll
+            for (int k = 0; k < D_IN; ++k) {
+                w1[k] = W1[k * H + j];
+                p[k] = 0.0f;
+            }
+#pragma unroll 1
+            for (int t0 = 0; t0 < nb; t0 += RG) {
+                const int rows = stage(t0);
+#pragma unroll 1
+                for (int r = 0; r < rows; ++r) {
+                    float x[D_IN], z = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < D_IN; ++k) {
+                        x[k] = xs[r * D_IN + k];
+                        z = fmaf(x[k], w1[k], z);
+                    }
+                    const float g = scale * res[t0 + r];         // eq. 15
+                    const bool on = z > 0.0f;                    // ReLU'(z) = [z > 0]
+                    q = fmaf(on ? z : 0.0f, g, q);               // eq. 16
+                    const float dz = on ? g * w2 : 0.0f;         // eq. 17
+#pragma unroll
+                    for (int k = 0; k < D_IN; ++k) p[k] = fmaf(x[k], dz, p[k]);   // eq. 18
+                }
+            }
+            if (j0 + tid < H) {
+                const float lr = COLD(lr);
+#pragma unroll
+                for (int k = 0; k < D_IN; ++k) W1[k * H + j] = w1[k] - lr * p[k];   // eq. 19
+                W2[j] = w2 - lr * q;
+            }
+        }
+        __syncthreads();   // the weights updated; red written
+        if (tid == 0) {
+            sse = red[0];
+            for (int w = 1; w < NW; ++w) sse += red[w];
+            flag_nonfinite(sse, COLD(err));
+            const float L = sse / (float)nb;
+            float *lo = COLD(loss), *sl = COLD(step_loss), *el = COLD(epoch_loss);
+            if (lo) lo[0] = L;
+            if (sl) sl[s] = L;
+            if (sb == 0) epoch_sse = 0.0;
+            epoch_sse += (double)sse;
+            if (el) {
+                el[e] = (float)(epoch_sse * (double)COLD(inv_n));
+                if (s + 1 == steps)
+                    for (int64_t x = e + 1; x < COLD(epochs); ++x) el[x] = 0.0f;
+            }
+        }
+        if (++sb == spe) {
+            sb = 0;
+            ++e;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // The kernel
 // ---------------------------------------------------------------------------
 // Compute wave w = wr + wu * WR takes row tiles [wr * RTW, (wr + 1) * RTW) and
@@ -433,7 +568,8 @@ template <class S, bool TR>
 __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     __shared__ int s_flags[8];   // 0: group x, 1: rank b, 2: plain local stores, 3: abort stamp, 4: active,
-                                 // 5: forward-done stamp (step + 1) of wave 0
+                                 // 5: forward-done stamp (step + 1) of wave 0, 6: workgroups out before,
+                                 // 7: the launch was given up
 
     constexpr int R = S::R, U = S::U, PR = S::PR, PX = S::PX, H = S::H;
     constexpr int WR = S::WR, WU = S::WU, NUW = S::NUW, RTW = S::RTW, NRW = S::NRW;
@@ -451,18 +587,24 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
                                                   __HIP_MEMORY_SCOPE_AGENT);
         const int rank_g = __hip_atomic_fetch_add(&a.reg[8], 1, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
-        // start barrier over the whole launch (once per call)
-        __hip_atomic_fetch_add(&a.reg[9], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t t_end = now_ticks() + a.timeout_ticks;
+        // start barrier over the whole launch (once per call): every workgroup finds it
+        // complete, or every workgroup finds it given up
+        if (a.start_ticks == 0)
+            __hip_atomic_fetch_or(&a.reg[9], START_GIVEN_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            __hip_atomic_fetch_add(&a.reg[9], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t t_end = now_ticks() + a.start_ticks;
         int ab = 0;
-        while (__hip_atomic_load(&a.reg[9], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) <
-               (int)gridDim.x) {
-            if (now_ticks() > t_end) {
-                __hip_atomic_store(a.err, (int32_t)MLP_ERR_TIMEOUT_CODE, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+        while (true) {
+            int here = __hip_atomic_load(&a.reg[9], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+            if (here & START_GIVEN_UP) {
                 ab = 1;
                 break;
             }
+            if (here >= (int)gridDim.x) break;
+            if (now_ticks() > t_end)   // a workgroup that arrives meanwhile makes it fail
+                __hip_atomic_compare_exchange_strong(&a.reg[9], &here, here | START_GIVEN_UP, __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // placement check: PR workgroups on each of XCDs 0..PX-1
         bool placed = !a.force_coherent;
@@ -493,6 +635,7 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
                      __builtin_amdgcn_readfirstlane(s_flags[3]) == 0;
     __syncthreads();
     if (tid == 0) {
+        s_flags[7] = s_flags[3];
         s_flags[3] = 0;   // from here on: the abort stamp
         s_flags[5] = 0;
     }
@@ -1138,15 +1281,23 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
         }
     }
 
-    // ---- teardown: the last workgroup out clears the registration counters ------
+    // ---- teardown: the last workgroup out trains alone if the launch was given up,
+    // and clears the registration counters -------------------------------------------
     __syncthreads();
+    if (tid == 0)
+        s_flags[6] = __hip_atomic_fetch_add(&a.reg[10], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_flags[6] != (int)gridDim.x - 1) return;
+    if (s_flags[7]) {
+        if (a.mode == 0)
+            train_alone<H>(lds);
+        else if (tid == 0)
+            __hip_atomic_store(a.err, (int32_t)MLP_ERR_TIMEOUT_CODE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (tid == 0) {
-        const int fin = __hip_atomic_fetch_add(&a.reg[10], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (fin == (int)gridDim.x - 1) {
-            for (int i = 0; i < 16; ++i)
-                __hip_atomic_store(&a.reg[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(a.abort, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        for (int i = 0; i < 16; ++i)
+            __hip_atomic_store(&a.reg[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.abort, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -1155,11 +1306,12 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
 // ---------------------------------------------------------------------------
 
 // The kernel needs every workgroup resident at once (its waits span the grid).
-// A cooperative launch guarantees that. With regular = true (a diagnostic hook
-// for profiler runs, MLP_REGULAR_LAUNCH=1) the same kernel is launched
-// normally: one workgroup per CU by its LDS request, grid <= CUs, and the
-// kernel's start barrier times out with MLP_ERR_TIMEOUT rather than wait
-// forever if some workgroup cannot start.
+// A cooperative launch checks that they fit the GPU; other work on it (another
+// stream's, another process's) may still keep some from starting, and a launch
+// whose workgroups have not all started after the start barrier's limit is given
+// up and its call done by one workgroup (train_alone). With regular = true (a
+// diagnostic hook for profiler runs, MLP_REGULAR_LAUNCH=1) the same kernel is
+// launched normally: one workgroup per CU by its LDS request, grid <= CUs.
 template <class S>
 static hipError_t launch_shape(hipStream_t stream, TrainArgs &a, bool regular) {
     void *args[] = {&a};
@@ -1266,6 +1418,8 @@ static const TrainPlan *all_plans(int *count) {
 //   MLP_PX=p, MLP_INST=i   restrict the choice to shapes with PX = p, or to
 //                          instance i (the parity tests run every instantiated
 //                          shape this way);
+//   MLP_START_TICKS=t      limit of the start barrier in 100 MHz ticks (0: every
+//                          launch is given up, and its last workgroup trains alone);
 //   MLP_FORCE_COHERENT=1   device-coherent exchange stores even when every group
 //                          sits on one XCD (tested bitwise against the default);
 //   MLP_TRACE=1            per-phase cycle sums of every workgroup into the
@@ -1326,6 +1480,8 @@ hipError_t launch_train(Ctx &c, TrainArgs &a) {
     a.abort = &c.ctl->abort;
     a.err = &c.ctl->err;
     a.timeout_ticks = 200000000ull;   // 2 s
+    const char *sl = getenv("MLP_START_TICKS");
+    a.start_ticks = sl ? strtoull(sl, nullptr, 10) : a.timeout_ticks;
     const char *tr = getenv("MLP_TRACE");
     a.phase = (tr && tr[0] == '1') ? reinterpret_cast<uint64_t *>(c.slots) : nullptr;
     c.phase_words = a.phase ? (int64_t)a.plan.grid * 2 * PHASE_WORDS : 0;
