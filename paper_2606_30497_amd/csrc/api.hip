@@ -106,6 +106,8 @@ extern "C" mlp_status mlp_init(mlp_t *out, int32_t d_in, int32_t hidden, int32_t
         delete c;
         return MLP_ERR_HIP;
     }
+    // test hook: plan as on a GPU with this many compute units
+    if (const char *cu = getenv("MLP_NUM_CU")) c->num_cu = atoi(cu);
     *out = c;
     return MLP_OK;
 }
@@ -188,10 +190,11 @@ static void prof_end(mlp_ctx *c) {
 
 // Under the FUSED strategy the persistent trainer runs every SGD step of a
 // training call in one launch; the tile path (one or two launches per step) serves
-// batches the trainer's plan cannot hold, and every call under the TILE strategy.
+// batches the trainer's plan cannot hold, GPUs (partitions of one) with fewer compute
+// units than its workgroups, and every call under the TILE strategy.
 static bool use_persistent(const mlp_ctx *c, int64_t batch, TrainPlan *pl) {
     if (c->strategy != MLP_STRATEGY_FUSED) return false;
-    return plan_train(c->hidden, batch, pl);
+    return plan_train(c->hidden, batch, pl) && pl->grid <= c->num_cu;
 }
 
 // A single gradient or step takes the tile path: the trainer's start (its

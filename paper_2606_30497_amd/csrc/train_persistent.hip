@@ -1501,7 +1501,7 @@ hipError_t launch_train(Ctx &c, TrainArgs &a) {
     a.tag_base = tp.base;
     c.tag_base = tp.next;
     const char *rl = getenv("MLP_REGULAR_LAUNCH");
-    const bool regular = rl && rl[0] == '1' && c.num_cu >= a.plan.grid;
+    const bool regular = rl && rl[0] == '1';
     hipError_t e = hipErrorInvalidValue;
     switch (a.plan.inst) {
 #define MLP_SHAPE_CASE(I, PX, PR, R, U) \

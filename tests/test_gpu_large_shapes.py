@@ -41,3 +41,20 @@ def test_large_shape(mlp, k):  # noqa: F811
 @pytest.mark.parametrize("px", [1, 2, 4])
 def test_exchange_protocol_of_32_workgroup_groups(px):
     assert violations(px, 32, steps=4) == []
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("h,B", [(64, 1000), (512, 2048), (256, 256)])
+def test_fewer_compute_units_than_workgroups(mlp, h, B):  # noqa: F811
+    """A partition of 32 compute units cannot hold the trainer's launch: the tile path
+    trains instead."""
+    n, lr = 3 * B - 5, 0.005
+    d = datagen.make_data(n, h, epochs=1, shuffle=True, seed=h + B)
+    with _env(MLP_NUM_CU=32):
+        ctx, _, _ = _ctx(mlp, d.W1, d.W2, B)
+        assert mlp.mlp_launch_info(ctx, n, B, 1)[1] == 2 * 3 + 1
+        g1, g2, gsl, gel = _train_gpu(mlp, d, B, lr, 1, perm=d.perm)
+    ref = oracle.train(d.X, d.Y, d.W1, d.W2, B, lr, 1, perm=d.perm)
+    check("W1 - W1_0", g1 - d.W1, ref["W1"] - d.W1.astype(np.float64), 1e-3)
+    check("W2 - W2_0", g2 - d.W2, ref["W2"] - d.W2.astype(np.float64), 1e-3)
+    assert np.all(np.abs(gsl - ref["step_loss"]) <= 1e-3 * ref["step_loss"])
