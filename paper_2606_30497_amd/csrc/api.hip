@@ -197,6 +197,28 @@ static bool use_persistent(const mlp_ctx *c, int64_t batch, TrainPlan *pl) {
     return plan_train(c->hidden, batch, pl) && pl->grid <= c->num_cu;
 }
 
+// Kernel launches of the tile path for `steps` steps over n rows, whole epochs but
+// perhaps the last: one a step of a batch one workgroup takes, else two.
+static int64_t tile_launches(const mlp_ctx *c, int64_t n, int64_t batch, int64_t steps) {
+    const int64_t spe = (n + batch - 1) / batch, tails = steps / spe;
+    const int64_t full = tile_workgroups(c->hidden, batch) == 1 ? 1 : 2;
+    const int64_t tail = tile_workgroups(c->hidden, n - (spe - 1) * batch) == 1 ? 1 : 2;
+    return (steps - tails) * full + tails * tail;
+}
+
+// Whether a training call of `steps` steps runs on the trainer. The larger batches'
+// shapes start all 256 compute units, which a call of a few steps does not repay:
+// those of up to six tile-path launches take the tile path (us a call there / on the
+// trainer: one step of 20 rows at h = 64 9.7 / 45; of 1,000 rows 12.5 / 46, three 25 /
+// 53, four 31 / 56 but 69 / 61 when each call is waited for; three of 2,048 rows at
+// h = 1024 65 / 68, four 86 / 74). The smaller shapes take every call.
+constexpr int64_t SHORT_LAUNCHES = 6;
+static bool trains_on_trainer(const mlp_ctx *c, int64_t n, int64_t batch, int64_t steps, TrainPlan *pl) {
+    if (!use_persistent(c, batch, pl)) return false;
+    return pl->inst < FIRST_LARGE_SHAPE || train_shape_forced() ||
+           tile_launches(c, n, batch, steps) > SHORT_LAUNCHES;
+}
+
 // A single gradient or step takes the tile path: the trainer's start (its
 // cooperative launch, registration and start barrier) outweighs the step (a step
 // of 64 rows at h = 256: 29 us on the trainer, 6.4 us on the tile path; of 4,096
@@ -290,7 +312,7 @@ mlp_status train_epochs_ctx(mlp_ctx *c, const float *X, const float *Y, int64_t 
     int64_t total = spe_all * (int64_t)epochs;
     if (max_steps >= 0 && max_steps < total) total = max_steps;
     TrainPlan pl;
-    if (total > 0 && total < ((int64_t)1 << 30) && use_persistent(c, batch, &pl)) {
+    if (total > 0 && total < ((int64_t)1 << 30) && trains_on_trainer(c, n, batch, total, &pl)) {
         TrainArgs t = train_args(c, pl);
         t.X = X; t.Y = Y; t.n_rows = n; t.perm = perm;
         t.n = n; t.batch = batch; t.steps = total; t.epochs = epochs;
@@ -376,23 +398,20 @@ extern "C" mlp_status mlp_launch_info(mlp_t c, int64_t n, int64_t batch, int32_t
     if (!c || !workgroups || !launches || n < 1 || batch < 1 || epochs < 1)
         return MLP_ERR_INVALID_ARG;
     TrainPlan pl;
-    if (use_persistent(c, batch, &pl)) {
+    const int64_t steps = ((n + batch - 1) / batch) * (int64_t)epochs;
+    if (trains_on_trainer(c, n, batch, steps, &pl)) {
         *workgroups = pl.grid;
         *launches = 1;
         return MLP_OK;
     }
-    const int64_t steps = ((n + batch - 1) / batch) * (int64_t)epochs;
     if (strategy_hostloop(c->strategy)) {
         // the largest product grid: 16 x 16 blocks over [batch x hidden]
         *workgroups = (int32_t)(((batch + 15) / 16) * ((c->hidden + 15) / 16));
         *launches = hostloop_launches_per_step(c->strategy) * steps + 1;
         return MLP_OK;
     }
-    // one launch a step for batches one workgroup takes, else two; and the
-    // epoch-loss clear
-    const int64_t tail = n - (n - 1) / batch * batch;
-    const int64_t per = tile_workgroups(c->hidden, batch) == 1 ? 1 : 2;
+    // and the epoch-loss clear
     *workgroups = tile_workgroups(c->hidden, batch);
-    *launches = (steps - epochs) * per + epochs * (tile_workgroups(c->hidden, tail) == 1 ? 1 : 2) + 1;
+    *launches = tile_launches(c, n, batch, steps) + 1;
     return MLP_OK;
 }

@@ -159,6 +159,7 @@ hipError_t hostloop_step(const Ctx &c, const float *X, int64_t n_rows, const flo
 
 // Persistent trainer
 bool plan_train(int hidden, int64_t batch, TrainPlan *plan);
+constexpr int FIRST_LARGE_SHAPE = 16;   // shapes from here on: the larger batches'
 bool train_shape_forced();   // a test hook restricts the shape choice
 size_t persist_words_xch();
 size_t persist_words_rs(int hidden);

@@ -1387,6 +1387,7 @@ static TrainPlan plan_of(int inst) {
     X(13, 4, 4, 16, 64)    /* 32-256-1,  batch <= 64,  four XCDs */   \
     X(14, 8, 4, 32, 32)    /* 32-256-1,  batch <= 128 */              \
     X(15, 8, 8, 32, 32)    /* 32-256-1,  batch <= 256 */              \
+    /* FIRST_LARGE_SHAPE */                                           \
     X(16, 8, 32, 32, 64)   /* 32-512-1,  batch <= 1024 */             \
     X(17, 8, 32, 64, 64)   /* 32-512-1,  batch <= 2048 */             \
     X(18, 8, 32, 128, 64)  /* 32-512-1,  batch <= 4096 */             \

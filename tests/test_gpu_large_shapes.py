@@ -8,7 +8,7 @@ import datagen
 import oracle
 from tests.parity import check
 from tests.test_exchange_protocol import violations
-from tests.test_gpu_parity import _check_grad, _ctx, _env, _train_gpu, mlp  # noqa: F401
+from tests.test_gpu_parity import _check_grad, _ctx, _env, _to, _train_gpu, mlp  # noqa: F401
 
 # (groups PX, workgroups per group PR, rows R, units U), from index 16 of the library's table
 LARGE_SHAPES = [(8, 32, 32, 64), (8, 32, 64, 64), (8, 32, 128, 64), (8, 32, 64, 128),
@@ -58,3 +58,30 @@ def test_fewer_compute_units_than_workgroups(mlp, h, B):  # noqa: F811
     check("W1 - W1_0", g1 - d.W1, ref["W1"] - d.W1.astype(np.float64), 1e-3)
     check("W2 - W2_0", g2 - d.W2, ref["W2"] - d.W2.astype(np.float64), 1e-3)
     assert np.all(np.abs(gsl - ref["step_loss"]) <= 1e-3 * ref["step_loss"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("h,B,n,E,launches", [
+    (64, 1000, 20, 1, 2), (64, 1000, 20, 6, 7), (64, 1000, 20, 7, 1),   # steps of one workgroup
+    (64, 1000, 1000, 3, 7), (64, 1000, 1000, 4, 1), (32, 4096, 8192, 1, 5),
+    (128, 300, 364, 2, 7), (128, 300, 365, 2, 1),                        # a tail of 64 rows, of 65
+    (512, 2048, 6000, 1, 7), (1024, 2048, 2048, 4, 1),
+    (256, 1000, 20, 1, 1), (64, 256, 20, 1, 1)])                        # the smaller shapes
+def test_short_calls(mlp, h, B, n, E, launches):  # noqa: F811
+    """Calls of a few steps of the larger batches run on the tile path (up to six launches
+    and the epoch-loss clear), longer ones on the trainer; either trains as the
+    oracle does, and the static entry does the same bitwise."""
+    lr = 0.005
+    d = datagen.make_data(n, h, epochs=E, shuffle=True, seed=h + n)
+    ctx, _, _ = _ctx(mlp, d.W1, d.W2, B)
+    assert mlp.mlp_launch_info(ctx, n, B, E)[1] == launches
+    g1, g2, gsl, gel = _train_gpu(mlp, d, B, lr, E, perm=d.perm)
+    ref = oracle.train(d.X, d.Y, d.W1, d.W2, B, lr, E, perm=d.perm)
+    check("W1 - W1_0", g1 - d.W1, ref["W1"] - d.W1.astype(np.float64), 1e-3)
+    check("W2 - W2_0", g2 - d.W2, ref["W2"] - d.W2.astype(np.float64), 1e-3)
+    assert np.all(np.abs(gsl - ref["step_loss"]) <= 1e-3 * ref["step_loss"])
+    assert np.all(np.abs(gel - ref["epoch_loss"]) <= 1e-3 * ref["epoch_loss"])
+    if h <= 256:
+        w1, w2 = _to(d.W1), _to(d.W2)
+        mlp.mlp_train_epochs_static(w1, w2, _to(d.X), _to(d.Y), B, lr, E, perm=_to(d.perm))
+        assert np.array_equal(w1.cpu().numpy(), g1) and np.array_equal(w2.cpu().numpy(), g2)

@@ -25,9 +25,9 @@ def _compare(d, B, lr, E, got, max_steps=-1):
 # every width; batches of one to four thousand rows, none a multiple of 64 (the rows
 # staged at a time), the last of an epoch shorter
 @pytest.mark.parametrize("ticks", [0, 1])
-@pytest.mark.parametrize("h,B,n,E", [(32, 1000, 2300, 2), (64, 300, 1000, 2), (128, 4093, 5000, 1),
-                                     (256, 1, 3, 2), (256, 4096, 9000, 1), (512, 700, 1500, 1),
-                                     (1024, 1030, 2100, 1)])
+@pytest.mark.parametrize("h,B,n,E", [(32, 1000, 2300, 2), (64, 300, 1000, 2), (128, 4093, 17000, 1),
+                                     (256, 1, 3, 2), (256, 4096, 9000, 1), (512, 700, 2900, 1),
+                                     (1024, 1030, 4200, 1)])
 def test_given_up_launch_trains(mlp, h, B, n, E, ticks):  # noqa: F811
     print("h", h, "B", B, "ticks", ticks, flush=True)
     d = datagen.make_data(n, h, epochs=E, shuffle=True, seed=h + B)
@@ -50,9 +50,9 @@ def test_given_up_launch_in_identity_order_and_short(mlp):  # noqa: F811
 
 
 def test_given_up_launch_flags_a_bad_row(mlp):  # noqa: F811
-    d = datagen.make_data(600, 64, epochs=1, shuffle=True, seed=6)
+    d = datagen.make_data(1500, 64, epochs=1, shuffle=True, seed=6)
     P = d.perm.copy()
-    P[0, 333] = 600
+    P[0, 333] = 1500
     with _env(MLP_START_TICKS=0):
         ctx, _, _ = _ctx(mlp, d.W1, d.W2, 300)
         mlp.mlp_train_epochs(ctx, _to(d.X), _to(d.Y), 300, 0.01, 1, perm=_to(P))
