@@ -246,7 +246,7 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
     using S = WideShape<H>;
     constexpr int NUT = S::NUT, WPT = S::WPT, TPI = S::TPI;
     __shared__ __attribute__((aligned(16))) float w2s[H];
-    __shared__ float part[2][S::WAVES][32];   // the waves' shares of a pass, by its parity
+    __shared__ float part[2][S::WAVES][64];   // the lanes' shares of a pass, by its parity
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -321,30 +321,36 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
     __syncthreads();   // w2s
 
     // eqs. 12-13 of register j of unit tile c: the lane's unit 8 (j / 4) + 4 lh + j % 4,
-    // summed by j % 4. ReLU as an integer max on the bits: every negative float (-0
+    // summed by j % 8. ReLU as an integer max on the bits: every negative float (-0
     // included) has a negative pattern and becomes +0, every positive one stays; one
     // instruction, where the float form costs two (a canonicalizing max first)
-    auto unit = [&](const f16v &c, int j, const float4 (&w2)[4], float (&y)[4]) __attribute__((always_inline)) {
+    auto unit = [&](const f16v &c, int j, const float4 (&w2)[4], float (&y)[8]) __attribute__((always_inline)) {
         const float4 q = w2[j / 4];
         const float ws[4] = {q.x, q.y, q.z, q.w};
-        y[j % 4] = fmaf(__int_as_float(max(__float_as_int(c[j]), 0)), ws[j % 4], y[j % 4]);
+        y[j % 8] = fmaf(__int_as_float(max(__float_as_int(c[j]), 0)), ws[j % 4], y[j % 8]);
     };
     auto load_w2 = [&](int u, float4 (&w2)[4]) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             w2[q] = *reinterpret_cast<const float4 *>(w2s + wu * S::UW + 32 * u + 8 * q + 4 * lh);
     };
-    // a pass's outputs: the row's sum over the wave's units, then over the waves
-    auto finish = [&](int64_t i, int par, const float (&y)[4]) __attribute__((always_inline)) {
+    // a pass's outputs: the row's sum over the lane's units, then in 64 bits over the two
+    // lanes of each wave and the waves (past two waves a half-wave takes half of them). Eight sums a lane
+    // and the 64 bits make up for k_forward's shorter chains: with four and 32 bits the
+    // outputs were 3-4 % farther from exact than k_forward's, with these 5 % nearer at
+    // 256 units and 20 % at 1024.
+    auto finish = [&](int64_t i, int par, const float (&y)[8]) __attribute__((always_inline)) {
         const int64_t r = row0(i) + lr;
-        const float s = xadd32((y[0] + y[1]) + (y[2] + y[3]));
-        if (lh == 0) part[par][wave][lr] = s;
+        part[par][wave][lane] = ((y[0] + y[1]) + (y[2] + y[3])) + ((y[4] + y[5]) + (y[6] + y[7]));
         __syncthreads();   // a wave is at most one pass ahead: the other parity's words
-        if (wu == 0 && lh == 0 && r >= 0 && r < B) {
-            float v = part[par][wt * WPT][lr];
+        if (wu == 0) {
+            constexpr int NQ = WPT == 2 ? 2 : WPT / 2;   // waves a lane adds
+            const float *p = part[par][wt * WPT + (WPT == 2 ? 0 : lh * NQ)];
+            double v = (double)p[lr] + (double)p[32 + lr];
 #pragma unroll
-            for (int q = 1; q < WPT; ++q) v += part[par][wt * WPT + q][lr];
-            ypred[r] = v;
+            for (int q = 1; q < NQ; ++q) v += (double)p[64 * q + lr] + (double)p[64 * q + 32 + lr];
+            if constexpr (WPT > 2) v = xadd32(v);
+            if (lh == 0 && r >= 0 && r < B) ypred[r] = (float)v;
         }
     };
 
@@ -354,7 +360,7 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
     // the previous pass's last unit tile and its sums so far (before the first pass,
     // of rows below 0: not stored)
     f16v prev = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float y[4] = {0.f, 0.f, 0.f, 0.f};
+    float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float4 w2[4];
     load_w2(NUT - 1, w2);
     int par = 0;
@@ -362,7 +368,7 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
         const float4 *pn = row_at(it + 2 * stride, ix);   // the rows two passes on
         ix = index_of(it + 3 * stride);
         uint32_t nx[2][3][4];
-        float yn[4] = {0.f, 0.f, 0.f, 0.f};
+        float yn[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < NUT; ++u) {
             constexpr int PX[6] = {2, 1, 0, 1, 0, 0}, PW[6] = {0, 1, 2, 0, 1, 0};
@@ -377,11 +383,11 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
                 c = mfma_bf16_32(w[u][k][PW[q]],
                                  u4v{xp[k][PX[q]][0], xp[k][PX[q]][1], xp[k][PX[q]][2], xp[k][PX[q]][3]}, c);
                 if (s < 8) {
-                    float(&ys)[4] = u == 0 ? y : yn;
+                    float(&ys)[8] = u == 0 ? y : yn;
                     unit(prev, 2 * s, w2, ys);
                     unit(prev, 2 * s + 1, w2, ys);
-                    pin(ys[(2 * s) % 4]);
-                    pin(ys[(2 * s + 1) % 4]);
+                    pin(ys[(2 * s) % 8]);
+                    pin(ys[(2 * s + 1) % 8]);
                 } else {   // a pair in two slots
                     const int pr = 2 * u + (s - 8) / 2, kk = pr / 4, t = pr % 4;
                     const float4 v = raw[pr / 2];
@@ -413,7 +419,7 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
         finish(it - stride, par, y);
         par ^= 1;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) y[v] = yn[v];
+        for (int v = 0; v < 8; ++v) y[v] = yn[v];
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll

@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <stdint.h>
+
 namespace mlp {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -27,6 +29,13 @@ __device__ __forceinline__ float xadd16(float v) {
 __device__ __forceinline__ float xadd32(float v) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ double xadd32(double v) {
+    const uint64_t w = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)w, (uint32_t)w, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(w >> 32), (uint32_t)(w >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
 }
 // sum over each row of 16 lanes, in every lane of the row: pairs (i, i^8),
 // (i, 7-i within 8), (i, i^2), (i, i^1)
