@@ -349,60 +349,6 @@ __device__ __forceinline__ void dw1_partial(const GemmArgs &g, int bx, int by, c
             dst[(int64_t)(16 * it + 4 * lq + v) * g.N + ub + 16 * u + li] = p[u][v];
 }
 
-// The mask operand of a MASK epilogue, in the layout of the accumulators (clamped
-// addresses, no lane condition).
-template <int TM, int TN, int NI, int NJ>
-__device__ __forceinline__ void load_mask(const GemmArgs &g, int bx, int by, float (&gm)[NI][NJ][4]) {
-    const AccLayout<TM, TN> at;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int n = by * TN + at.col(j);
-            const int nc = n < g.N ? n : g.N - 1;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t m = (int64_t)bx * TM + at.row(i) + v;
-                gm[i][j][v] = g.G[(m < g.M ? m : g.M - 1) * g.ldg + nc];
-            }
-        }
-}
-
-// The epilogue of one output tile, acc (plus lo in the bf16x3 flavour).
-template <int EP, int TM, int TN, bool BF3, int NI, int NJ, int GI, int GJ>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int bx, int by, int bz,
-                                              f4 (&acc)[NI][NJ], const f4 (&lo)[NI][NJ],
-                                              const float (&gm)[GI][GJ][4], float *__restrict__ lds) {
-    static_assert(NI == AccLayout<TM, TN>::NI && NJ == AccLayout<TM, TN>::NJ, "layout");
-    const AccLayout<TM, TN> at;
-    constexpr bool MASKED = EP == EP_MASK || EP == EP_MASK_DW1;
-    const int64_t m0 = (int64_t)bx * TM, M = g.M;
-    const int n0 = by * TN, N = g.N, ldc = g.ldc;
-    float *Cz = g.C + (int64_t)bz * g.c_split;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int n = n0 + at.col(j);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t m = m0 + at.row(i) + v;
-                if (m >= M || n >= N) {
-                    if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = 0.0f;   // no row: no term
-                    continue;
-                }
-                float r = BF3 ? acc[i][j][v] + lo[i][j][v] : acc[i][j][v];
-                // eq. 12; a NaN passes (a diverged step must reach the loss: an
-                // infinite operand leaves NaN in its split parts)
-                if constexpr (EP == EP_RELU) r = r <= 0.0f ? 0.0f : r;
-                if constexpr (MASKED) r = gm[i][j][v] > 0.0f ? r : 0.0f;    // eq. 17
-                if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = r;
-                Cz[m * ldc + n] = r;
-            }
-        }
-    if constexpr (EP == EP_MASK_DW1) dw1_partial<TM, TN, NI, NJ>(g, bx, by, acc, lds);
-}
-
 // One output tile (bx, by) of split bz; lds holds gemm_lds_floats(TM, TN, BF3).
 template <int OP, int EP, int TM, int TN, bool BF3>
 __device__ __forceinline__ void gemm_block(const GemmArgs &g, int bx, int by, int bz,
@@ -413,7 +359,8 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &g, int bx, int by, in
     float *Bs2[2] = {lds + 2 * tile_floats(TM, BF3), lds + 2 * tile_floats(TM, BF3) + tile_floats(TN, BF3)};
     const float *__restrict__ A = g.A;
     const float *__restrict__ B = g.B;
-    const int lda = g.lda, ldb = g.ldb, N = g.N;
+    const float *__restrict__ G = g.G;
+    const int lda = g.lda, ldb = g.ldb, ldc = g.ldc, ldg = g.ldg, N = g.N;
     const int64_t M = g.M, K = g.K, kc = g.kc;
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
@@ -450,7 +397,20 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &g, int bx, int by, in
     // so that its loads overlap the K loop instead of each waiting at the end
     constexpr bool MASKED = EP == EP_MASK || EP == EP_MASK_DW1;
     float gm[MASKED ? MI : 1][MASKED ? NJ : 1][4];
-    if constexpr (MASKED) load_mask<TM, TN>(g, bx, by, gm);
+    if constexpr (MASKED) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int n = n0 + wn * (TN / 2) + j * 16 + li;
+                const int nc = n < N ? n : N - 1;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t m = m0 + wm * (TM / 2) + i * 16 + 4 * lq + v;
+                    gm[i][j][v] = G[(m < M ? m : M - 1) * ldg + nc];
+                }
+            }
+    }
     // fp32: eight k steps of 4 on the matrix cores.
     // bf16x3: lane (li, lq) reads k in [8 lq, 8 lq + 8) of row li of each 16-row
     // operand tile, for every part. The leading part product a0 b0 accumulates
@@ -531,7 +491,30 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &g, int bx, int by, in
             mfma_chunk(buf);
         }
     }
-    gemm_epilogue<EP, TM, TN, BF3>(g, bx, by, bz, acc, lo, gm, lds);
+    // ---- epilogue: lane holds C[4 lq + v][li] of each 16 x 16 tile ----
+    float *Cz = g.C + (int64_t)bz * g.c_split;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int n = n0 + wn * (TN / 2) + j * 16 + li;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t m = m0 + wm * (TM / 2) + i * 16 + 4 * lq + v;
+                if (m >= M || n >= N) {
+                    if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = 0.0f;   // no row: no term
+                    continue;
+                }
+                float r = BF3 ? acc[i][j][v] + lo[i][j][v] : acc[i][j][v];
+                // eq. 12; a NaN passes (a diverged step must reach the loss: an
+                // infinite operand leaves NaN in its split parts)
+                if constexpr (EP == EP_RELU) r = r <= 0.0f ? 0.0f : r;
+                if constexpr (MASKED) r = gm[i][j][v] > 0.0f ? r : 0.0f;    // eq. 17
+                if constexpr (EP == EP_MASK_DW1) acc[i][j][v] = r;
+                Cz[m * ldc + n] = r;
+            }
+        }
+    if constexpr (EP == EP_MASK_DW1) dw1_partial<TM, TN, MI, NJ>(g, bx, by, acc, lds);
 }
 
 // ---- 128 x 128 tiles -----------------------------------------------------------
@@ -723,9 +706,46 @@ __device__ __forceinline__ void gemm_block128(const GemmArgs &g, int bx, int by,
                 r[i][j][v] = acc[i / 4][j][4 * (i % 4) + v];
                 rl[i][j][v] = lo[i / 4][j][4 * (i % 4) + v];
             }
+    // the epilogue of gemm_block, in its own accumulator layout (as one function for
+    // both, the smaller tiles took more registers, and the 64 x 64 pair spilled three)
+    const AccLayout<BT, BT> at;
+    const int N = g.N, ldc = g.ldc;
     float gm[MASKED ? 8 : 1][MASKED ? 2 : 1][4];
-    if constexpr (MASKED) load_mask<BT, BT>(g, bx, by, gm);
-    gemm_epilogue<EP, BT, BT, true>(g, bx, by, bz, r, rl, gm, lds);
+    if constexpr (MASKED) {   // clamped addresses, no lane condition
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int n = n0 + at.col(j);
+                const int nc = n < N ? n : N - 1;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int64_t m = m0 + at.row(i) + v;
+                    gm[i][j][v] = g.G[(m < M ? m : M - 1) * g.ldg + nc];
+                }
+            }
+    }
+    float *Cz = g.C + (int64_t)bz * g.c_split;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int n = n0 + at.col(j);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t m = m0 + at.row(i) + v;
+                if (m >= M || n >= N) {
+                    if constexpr (EP == EP_MASK_DW1) r[i][j][v] = 0.0f;   // no row: no term
+                    continue;
+                }
+                float c = r[i][j][v] + rl[i][j][v];
+                if constexpr (EP == EP_RELU) c = c <= 0.0f ? 0.0f : c;      // eq. 12, a NaN passes
+                if constexpr (MASKED) c = gm[i][j][v] > 0.0f ? c : 0.0f;    // eq. 17
+                if constexpr (EP == EP_MASK_DW1) r[i][j][v] = c;
+                Cz[m * ldc + n] = c;
+            }
+        }
+    if constexpr (EP == EP_MASK_DW1) dw1_partial<BT, BT, 8, 2>(g, bx, by, r, lds);
 }
 
 template <int OP, int EP>

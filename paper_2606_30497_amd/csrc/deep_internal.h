@@ -79,7 +79,7 @@ __device__ __forceinline__ void gather_one(const GatherArgs &g, int64_t e) {
 // The batch loss (eq. 14) of nb squared residuals by one workgroup of 256
 // threads: thread i sums rows i, i + 256, ... (32 loads in flight), then a fixed
 // binary tree; step and epoch loss as in the one-layer paths.
-__device__ __forceinline__ void batch_loss(const float *__restrict__ sq, int64_t nb, const ReduceArgs &ra) {
+__device__ __forceinline__ void batch_loss(const float *sq, int64_t nb, const ReduceArgs &ra) {
     constexpr int U = 32;
     __shared__ float red[256];
     const int i = threadIdx.x;
