@@ -228,9 +228,10 @@ static bool single_on_trainer(const mlp_ctx *c, int64_t batch, TrainPlan *pl) {
 }
 
 // One host-driven step under the TILE, OPTIMIZED or BASELINE strategy.
-static hipError_t host_step(const mlp_ctx *c, const float *X, int64_t n_rows, const float *Y,
+static hipError_t host_step(mlp_ctx *c, const float *X, int64_t n_rows, const float *Y,
                             const int32_t *idx, int64_t idx_off, int64_t nb, const ReduceArgs &a) {
     if (strategy_hostloop(c->strategy)) return hostloop_step(*c, X, n_rows, Y, idx, idx_off, nb, a);
+    c->phase_words = 0;   // the slots held a traced call's phase sums
     return tile_step(*c, X, n_rows, Y, idx, idx_off, nb, a);
 }
 

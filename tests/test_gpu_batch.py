@@ -8,7 +8,7 @@ import torch
 import datagen
 import oracle
 from tests.parity import rel
-from tests.test_gpu_parity import _check_grad, _ctx, _rows, _to, mlp  # noqa: F401
+from tests.test_gpu_parity import _check_grad, _ctx, _env, _rows, _to, mlp  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +65,17 @@ def test_forward_of_many_rows(mlp, h, B, gather):  # noqa: F811
         with pytest.raises(mlp.MLPError) as e:
             mlp.mlp_check_errors(ctx)
         assert e.value.status == -6
+
+
+def test_phase_sums_are_not_read_past_their_call(mlp):  # noqa: F811
+    """A traced training call's phase sums lie where the gradient's partials go: after a
+    gradient there are none to copy."""
+    d = datagen.make_data(5000, 256, epochs=1, shuffle=False, seed=3)
+    ctx, _, _ = _ctx(mlp, d.W1, d.W2, 256)
+    X, Y = _to(d.X), _to(d.Y)
+    with _env(MLP_TRACE=1):
+        mlp.mlp_train_epochs(ctx, X, Y, 256, 0.001, 1)
+    c = mlp.mlp_phase_cycles(ctx)
+    assert c is not None and np.all(c[:, :, 0].max(axis=0) == 20 - 8)   # steps from the eighth on
+    mlp.mlp_backward(ctx, X, Y, B=100)
+    assert mlp.mlp_phase_cycles(ctx) is None
