@@ -18,6 +18,11 @@ Two kinds of inputs:
   1e-3; the 1024-wide large-tile case also keeps its whole batch (its point is
   the tile shapes of 2100 rows) and the 1e-3 bar. At L = 1 the network is the paper's
   and the gradients meet 1e-4 after the kink alignment of tests/parity.py.
+
+Nets up to 256 units run a panel of rows through all layers in one launch (deep_panel.hip)
+where that is the faster, and the sequence of GEMM launches (deep.hip) elsewhere and on
+a workspace without the panels' part. The tests of those widths run both ways (`path`);
+wider nets have the GEMM launches only.
 """
 import numpy as np
 import pytest
@@ -106,15 +111,31 @@ def _dyadic(rng, n, h, L):
     return X, Y, P
 
 
+_GEMM_ONLY = [False]
+
+
+@pytest.fixture(params=["full", "gemm"])
+def path(request):
+    """full: the workspace mlp_deep_workspace_bytes names; gemm: one byte less, on which
+    every call runs as GEMM launches."""
+    _GEMM_ONLY[0] = request.param == "gemm"
+    yield request.param
+    _GEMM_ONLY[0] = False
+
+
 def _ctx(mlp, P, h, L, max_batch):
     p = _to(P.astype(np.float32))
-    return mlp.mlp_deep_init(p, h, L, max_batch), p
+    ws = None
+    if _GEMM_ONLY[0]:
+        need = mlp.load().mlp_deep_workspace_bytes(D, h, L, max_batch)
+        ws = torch.empty(need - 1, dtype=torch.uint8, device="cuda")
+    return mlp.mlp_deep_init(p, h, L, max_batch, workspace=ws), p
 
 
 # --- forward -------------------------------------------------------------------
 
 @pytest.mark.parametrize("h,L", [(64, 1), (64, 2), (64, 3), (128, 2), (192, 2)])
-def test_forward_dyadic_is_exact(mlp, h, L):
+def test_forward_dyadic_is_exact(mlp, h, L, path):
     rng = np.random.default_rng(10 * h + L)
     X, Y, P = _dyadic(rng, 1000, h, L)
     ctx, _ = _ctx(mlp, P, h, L, 256)             # 1000 rows: four chunks of max_batch
@@ -155,7 +176,7 @@ def test_forward_gaussian(mlp, h, L):
 
 @pytest.mark.parametrize("h,L", [(64, 1), (64, 2), (64, 3), (128, 3)])
 @pytest.mark.parametrize("B", [1, 16, 64, 256])
-def test_gradients_dyadic(mlp, h, L, B):
+def test_gradients_dyadic(mlp, h, L, B, path):
     rng = np.random.default_rng(1000 * L + 7 * h + B)
     X, Y, P = _dyadic(rng, 600, h, L)
     ctx, _ = _ctx(mlp, P, h, L, 256)
@@ -170,7 +191,7 @@ def test_gradients_dyadic(mlp, h, L, B):
 
 @pytest.mark.parametrize("h,L", [(64, 2), (256, 2), (256, 3)])
 @pytest.mark.parametrize("B", [7, 160, 1000])
-def test_gradients_gaussian(mlp, h, L, B):
+def test_gradients_gaussian(mlp, h, L, B, path):
     """Loss of a random batch at 1e-5; gradients of a batch of B kink-free rows
     (drawn from up to 8 B random rows) at 1e-5, as in the dyadic cases (measured
     0.7-7e-7: with the masks settled only the fp32 sums round)."""
@@ -249,13 +270,15 @@ def test_widths_off_the_power_of_two_grid(mlp, h):
     mlp.mlp_deep_check_errors(ctx)
 
 
-def test_large_batch_split_plans(mlp):
-    """A batch of 20,000 kink-free rows at 32-256x2-1: the back-propagation runs
-    64 x 64 tiles beside a weight gradient on 32 x 64 tiles (16 row chunks of
-    1280 rows, the last one ragged) in one launch, dW_1 comes in 313 partials
-    (one per 64-row tile), and the output layer in 209 chunks of 96 rows (its
-    cap of 256 chunks reached), so the update kernel's loops run many batches
-    and a tail. Gradient and loss at 1e-5."""
+def test_large_batch_split_plans(mlp, path):
+    """A batch of 20,000 kink-free rows at 32-256x2-1. As GEMM launches: the
+    back-propagation runs 64 x 64 tiles beside a weight gradient on 32 x 64 tiles
+    (16 row chunks of 1280 rows, the last one ragged) in one launch, dW_1 comes in
+    313 partials (one per 64-row tile), and the output layer in 209 chunks of 96
+    rows (its cap of 256 chunks reached), so the update kernel's loops run many
+    batches and a tail. As panels: 625 of 32 rows, three rounds of 256 workgroups,
+    and the row chunks of the weight gradient at their cap of 16.
+    Gradient and loss at 1e-5."""
     h, L, B = 256, 2, 20000
     rng = np.random.default_rng(20000)
     d = datagen.make_data(60000, 32, seed=8, with_perm=False)
@@ -275,7 +298,7 @@ def test_large_batch_split_plans(mlp):
 
 @pytest.mark.parametrize("h,L", [(64, 8), (128, 8)])
 @pytest.mark.parametrize("B", [7, 160, 1000])
-def test_gradients_gaussian_eight_layers(mlp, h, L, B):
+def test_gradients_gaussian_eight_layers(mlp, h, L, B, path):
     """Eight layers: the rounding bound of _kink_free compounds with depth
     (each layer multiplies it by about sum_k |W_kj|), so no row is provably
     kink-free; the whole batch is compared at 1e-3, the loss at 1e-5."""
@@ -315,7 +338,7 @@ def test_large_tiles(mlp, B):
 
 
 @pytest.mark.parametrize("h", [64, 256])
-def test_one_layer_meets_the_main_bar(mlp, h):
+def test_one_layer_meets_the_main_bar(mlp, h, path):
     """L = 1 is the paper's network: gradients within 1e-4 of the shallow oracle
     after the kink alignment used for the main path."""
     d = datagen.make_data(5000, h, seed=300 + h, with_perm=False)
@@ -350,7 +373,7 @@ def _train(mlp, X, Y, P, h, L, batch, lr, epochs, perm=None, max_steps=-1):
 
 
 @pytest.mark.parametrize("h,L", [(64, 2), (64, 3), (256, 2)])
-def test_train_epochs_with_shuffle_and_tail(mlp, h, L):
+def test_train_epochs_with_shuffle_and_tail(mlp, h, L, path):
     n, B, E, lr = 1000, 128, 2, 2.0 ** -7                 # tail of 104 rows each epoch
     rng = np.random.default_rng(h + 10 * L)
     X, Y, P = _dyadic(rng, n, h, L)
@@ -364,7 +387,7 @@ def test_train_epochs_with_shuffle_and_tail(mlp, h, L):
     assert np.all(np.abs(gel - ref["epoch_loss"]) <= 1e-3 * ref["epoch_loss"])
 
 
-def test_train_eight_layers(mlp):
+def test_train_eight_layers(mlp, path):
     """The deepest net the API takes (L = 8, h = 64), two shuffled epochs of
     1500 rows at batch 256 (tail of 220) on the evaluation recipe. The oracle
     itself moves by under 1e-6 when W0 is perturbed by 1e-7, so the bars are
@@ -381,7 +404,7 @@ def test_train_eight_layers(mlp):
     assert np.all(np.abs(gel - ref["epoch_loss"]) <= 1e-4 * ref["epoch_loss"])
 
 
-def test_train_gaussian_workload_batch(mlp):
+def test_train_gaussian_workload_batch(mlp, path):
     """Three SGD steps of a 32-256-256-256-1 net at batch 4096 on the evaluation
     recipe (He-normal weights, sin target), against the oracle."""
     h, L, B, lr = 256, 3, 4096, 0.002
@@ -394,7 +417,7 @@ def test_train_gaussian_workload_batch(mlp):
     assert np.all(np.abs(gsl - ref["step_loss"]) <= 1e-4 * ref["step_loss"])
 
 
-def test_zero_learning_rate(mlp):
+def test_zero_learning_rate(mlp, path):
     """lr = 0: the parameters stay bitwise as they were through a shuffled epoch
     (four steps, the last one a tail) and every step's loss is the batch MSE at
     the initial parameters, as the oracle's run with lr = 0 gives it."""
@@ -409,7 +432,7 @@ def test_zero_learning_rate(mlp):
     assert abs(gel[0] - ref["epoch_loss"][0]) <= 1e-5 * ref["epoch_loss"][0]
 
 
-def test_deterministic(mlp):
+def test_deterministic(mlp, path):
     rng = np.random.default_rng(3)
     d = datagen.make_data(3000, 32, epochs=2, seed=8)
     P = _gauss_net(rng, 128, 3)
@@ -421,7 +444,7 @@ def test_deterministic(mlp):
 
 # --- errors --------------------------------------------------------------------
 
-def test_errors(mlp):
+def test_errors(mlp, path):
     rng = np.random.default_rng(4)
     P = _gauss_net(rng, 64, 2)
     ctx, p = _ctx(mlp, P, 64, 2, 64)
@@ -446,7 +469,7 @@ def test_errors(mlp):
     assert torch.equal(before, p)
 
 
-def test_divergence_is_flagged(mlp):
+def test_divergence_is_flagged(mlp, path):
     """As in the one-layer path: a learning rate of 1e30 overflows the next
     batch loss and mlp_deep_check_errors reports MLP_ERR_NONFINITE once."""
     h, L = 64, 2

@@ -1,10 +1,10 @@
 """fp32 on device: the split products are at least as accurate as plain fp32.
 
-The trainer, the forward pass and the deep path's 64 x 64 GEMM tiles form their
-fp32 products on the bf16 matrix cores: every fp32 operand is split exactly
-into three bf16 parts, the six part products with i + j <= 2 (each exact in
-fp32) are accumulated in fp32, and only the three smallest part products (at
-most 2.01 u |x y| together, u = 2^-24) are dropped. Data, accumulation and
+The trainer, the tile path, the forward pass and the deep path's panels and large
+GEMM tiles form their fp32 products on the bf16 matrix cores: every fp32 operand
+is split exactly into three bf16 parts, the six part products with i + j <= 2
+(each exact in fp32) are accumulated in fp32, and only the three smallest part
+products (at most 2.01 u |x y| together, u = 2^-24) are dropped. Data, accumulation and
 results are fp32; this is not a reduced-precision substitute for fp32.
 
 These tests put that to a measurement on the evaluation workloads' data: the
@@ -23,6 +23,7 @@ import datagen
 import oracle
 from tests.parity import align_kinks, rel, relmax
 from tests.test_gpu_deep import _gauss_net, _kink_free
+from tests.test_gpu_parity import _env
 
 pytestmark = pytest.mark.gpu
 
@@ -67,8 +68,16 @@ def _compare(name, dev, f32, ref, ref_f32=None):
     assert md <= RATIO * mf, (name, "max elementwise", md, mf)
 
 
-@pytest.mark.parametrize("k", [4, 3])   # 32-256-1 at batch 4096; 32-1024-1 at batch 1024
-def test_trainer_and_forward_at_fp32_level(mlp, k):
+# 32-256-1 at batch 4096; 32-1024-1 at batch 1024. A gradient runs on the tile path; the
+# trainer's arithmetic is measured through its gradient mode, which a test reaches by
+# naming one of its shapes (0 and 5: the ones that train these batches).
+@pytest.mark.parametrize("k,inst", [(4, None), (3, None), (4, 0), (3, 5)])
+def test_trainer_and_forward_at_fp32_level(mlp, k, inst):
+    with _env(MLP_INST=inst):
+        _at_fp32_level(mlp, k)
+
+
+def _at_fp32_level(mlp, k):
     w = datagen.WORKLOADS[k]
     n = 200_000
     d = datagen.make_data(n, w.hidden, seed=w.seed, with_perm=False)
@@ -112,15 +121,18 @@ def _f32_deep(X, Y, P, h, L):
     return yp, np.concatenate([dW.ravel() for dW in dWs] + [dwo])
 
 
-def test_deep_wide_tiles_at_fp32_level(mlp):
-    """32-1024x2-1 at a batch of 2100 kink-free rows: every product that runs
-    64 x 64 tiles (the forward, the W_2 gradient paired with the
-    back-propagation) is formed from split parts."""
-    h, L, B = 1024, 2, 2100
+@pytest.mark.parametrize("h,B", [(1024, 2100), (256, 4096), (192, 8200)])
+def test_deep_products_at_fp32_level(mlp, h, B):
+    """Two layers at a batch of kink-free rows: at 1024 units every product that runs
+    64 x 64 tiles (the forward, the W_2 gradient paired with the back-propagation), up
+    to 256 units every product of the panels (of 16 and of 64 rows) and of their weight
+    gradients is formed from split parts."""
+    L = 2
     rng = np.random.default_rng(4096)
-    d = datagen.make_data(5000, 32, seed=6, with_perm=False)
+    n = 5000 if B < 5000 else 2 * B
+    d = datagen.make_data(n, 32, seed=6, with_perm=False)
     P = _gauss_net(rng, h, L)
-    rows = _kink_free(d.X, P, h, L, rng.integers(0, 5000, size=8 * B).astype(np.int32))[:B]
+    rows = _kink_free(d.X, P, h, L, rng.integers(0, n, size=8 * B).astype(np.int32))[:B]
     assert len(rows) == B
     p = _to(P)
     ctx = mlp.mlp_deep_init(p, h, L, B)
@@ -131,8 +143,8 @@ def test_deep_wide_tiles_at_fp32_level(mlp):
     ref, _, _ = oracle.deep_grad(d.X, d.Y, P, 32, h, L, idx=rows)
     ry = oracle.deep_forward(d.X, P, 32, h, L, idx=rows)
     fy, fg = _f32_deep(d.X[rows], d.Y[rows], P, h, L)
-    _compare("deep Ypred (h=1024)", yp, fy, ry)
-    _compare("deep gradient (h=1024)", dP.cpu().numpy(), fg, ref)
+    _compare("deep Ypred (h=%d)" % h, yp, fy, ry)
+    _compare("deep gradient (h=%d)" % h, dP.cpu().numpy(), fg, ref)
 
 
 @pytest.mark.parametrize("h", [256, 512, 1024])
