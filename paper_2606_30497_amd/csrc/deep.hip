@@ -1125,11 +1125,15 @@ static hipError_t gemm(hipStream_t st, const float *A, int lda, const float *B, 
     bool small;
     const GemmArgs g = gemm_args(A, lda, B, ldb, C, ldc, c_split, M, N, K, splits, kc, G, ldg, &small);
     const dim3 grid((unsigned)g.gx, (unsigned)g.gy, (unsigned)g.gz);
-    if (fits128(g)) {
-        const GemmArgs w = tiles128(g);
-        hipLaunchKernelGGL((k_gemm128<OP, EP>), dim3((unsigned)w.gx, (unsigned)w.gy, (unsigned)w.gz), dim3(256),
-                           BT_LDS, st, w);
-    } else if (small && (int64_t)g.gx * g.gy * g.gz < 4 * GEMM_CUS) {
+    if constexpr (OP == OP_NN) {   // a lone weight gradient has 32 rows: never on these tiles
+        if (fits128(g)) {
+            const GemmArgs w = tiles128(g);
+            hipLaunchKernelGGL((k_gemm128<OP, EP>), dim3((unsigned)w.gx, (unsigned)w.gy, (unsigned)w.gz), dim3(256),
+                               BT_LDS, st, w);
+            return hipGetLastError();
+        }
+    }
+    if (small && (int64_t)g.gx * g.gy * g.gz < 4 * GEMM_CUS) {
         // 32 x 32 tiles where 32 x 64 ones would leave fewer than four
         // workgroups per CU
         GemmArgs gn = g;
