@@ -218,15 +218,17 @@ static hipError_t launch_forward_h(const Ctx &c, const float *X, int64_t n_rows,
 // A wave takes 128 units (four tiles of 32) and 32 rows a pass, as Z1^T: the weights
 // are the A operand of v_mfma_f32_32x32x16_bf16, the rows its B operand, so lane l
 // holds row l % 32 and, in its registers, units: ReLU, the W2 product and the sum
-// over the wave's units stay in the lane, and one half-wave exchange ends them. The
+// over the wave's units stay in the lane, and one exchange in LDS ends them. The
 // vector work of a pass (its epilogues and the next rows' splits, about five
 // instructions an MFMA) is issued between the MFMAs, one unit tile behind: on a bare
 // loop with constant operands 24 of these MFMAs and 160 vector instructions take 467
 // ns interleaved and 510 in two blocks, 48 16x16x32 ones 520 and 570.
-// Bound by the matrix cores' power: 10M rows through 256 units run at 220 TFLOP/s of
-// fp32 work, 1,320 of bf16, where a large library bf16 product reaches 1,150 on the
-// same card. Against k_forward, 4M rows: 256 units 341 -> 317 us, 512 642 -> 602, 1024
-// 1,303 -> 1,159.
+// Bound by the card's power: 10M rows through 256 units always take 1.26M clocks, three
+// quarters of them with the matrix cores busy, but at 1.7 GHz and, run after run, less
+// (705-800 us; of zeros, which draw less, 527 us: 2.4 GHz). That is 210-235 TFLOP/s of
+// fp32 work, 1,270-1,400 of bf16; a large library bf16 product reaches 1,430 on the same
+// card, and 1,800 of zeros. Against k_forward on one box, 4M rows: 256 units 341 -> 317
+// us, 512 642 -> 602, 1024 1,303 -> 1,159 (before the 64-bit sums below).
 template <int H>
 struct WideShape {
     static constexpr int UW = 128;                    // units per wave
@@ -321,13 +323,13 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
     __syncthreads();   // w2s
 
     // eqs. 12-13 of register j of unit tile c: the lane's unit 8 (j / 4) + 4 lh + j % 4,
-    // summed by j % 8. ReLU as an integer max on the bits: every negative float (-0
+    // summed by j % 4. ReLU as an integer max on the bits: every negative float (-0
     // included) has a negative pattern and becomes +0, every positive one stays; one
     // instruction, where the float form costs two (a canonicalizing max first)
-    auto unit = [&](const f16v &c, int j, const float4 (&w2)[4], float (&y)[8]) __attribute__((always_inline)) {
+    auto unit = [&](const f16v &c, int j, const float4 (&w2)[4], float (&y)[4]) __attribute__((always_inline)) {
         const float4 q = w2[j / 4];
         const float ws[4] = {q.x, q.y, q.z, q.w};
-        y[j % 8] = fmaf(__int_as_float(max(__float_as_int(c[j]), 0)), ws[j % 4], y[j % 8]);
+        y[j % 4] = fmaf(__int_as_float(max(__float_as_int(c[j]), 0)), ws[j % 4], y[j % 4]);
     };
     auto load_w2 = [&](int u, float4 (&w2)[4]) __attribute__((always_inline)) {
 #pragma unroll
@@ -335,13 +337,13 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
             w2[q] = *reinterpret_cast<const float4 *>(w2s + wu * S::UW + 32 * u + 8 * q + 4 * lh);
     };
     // a pass's outputs: the row's sum over the lane's units, then in 64 bits over the two
-    // lanes of each wave and the waves (past two waves a half-wave takes half of them). Eight sums a lane
-    // and the 64 bits make up for k_forward's shorter chains: with four and 32 bits the
-    // outputs were 3-4 % farther from exact than k_forward's, with these 5 % nearer at
-    // 256 units and 20 % at 1024.
-    auto finish = [&](int64_t i, int par, const float (&y)[8]) __attribute__((always_inline)) {
+    // lanes of each wave and the waves (past two waves a half-wave takes half of them).
+    // The 64 bits make up for k_forward's shorter chains: with 32 the outputs were 3-4 %
+    // farther from exact than k_forward's, so they are 2 % nearer at 256 units and 15 % at
+    // 1024, for 0.2-0.4 % of the time (eight sums a lane: 7 and 19 %, for 0.4-0.8 %).
+    auto finish = [&](int64_t i, int par, const float (&y)[4]) __attribute__((always_inline)) {
         const int64_t r = row0(i) + lr;
-        part[par][wave][lane] = ((y[0] + y[1]) + (y[2] + y[3])) + ((y[4] + y[5]) + (y[6] + y[7]));
+        part[par][wave][lane] = (y[0] + y[1]) + (y[2] + y[3]);
         __syncthreads();   // a wave is at most one pass ahead: the other parity's words
         if (wu == 0) {
             constexpr int NQ = WPT == 2 ? 2 : WPT / 2;   // waves a lane adds
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
     // the previous pass's last unit tile and its sums so far (before the first pass,
     // of rows below 0: not stored)
     f16v prev = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float y[4] = {0.f, 0.f, 0.f, 0.f};
     float4 w2[4];
     load_w2(NUT - 1, w2);
     int par = 0;
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
         const float4 *pn = row_at(it + 2 * stride, ix);   // the rows two passes on
         ix = index_of(it + 3 * stride);
         uint32_t nx[2][3][4];
-        float yn[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        float yn[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < NUT; ++u) {
             constexpr int PX[6] = {2, 1, 0, 1, 0, 0}, PW[6] = {0, 1, 2, 0, 1, 0};
@@ -383,11 +385,11 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
                 c = mfma_bf16_32(w[u][k][PW[q]],
                                  u4v{xp[k][PX[q]][0], xp[k][PX[q]][1], xp[k][PX[q]][2], xp[k][PX[q]][3]}, c);
                 if (s < 8) {
-                    float(&ys)[8] = u == 0 ? y : yn;
+                    float(&ys)[4] = u == 0 ? y : yn;
                     unit(prev, 2 * s, w2, ys);
                     unit(prev, 2 * s + 1, w2, ys);
-                    pin(ys[(2 * s) % 8]);
-                    pin(ys[(2 * s + 1) % 8]);
+                    pin(ys[(2 * s) % 4]);
+                    pin(ys[(2 * s + 1) % 4]);
                 } else {   // a pair in two slots
                     const int pr = 2 * u + (s - 8) / 2, kk = pr / 4, t = pr % 4;
                     const float4 v = raw[pr / 2];
@@ -419,7 +421,7 @@ __global__ __launch_bounds__(64 * WideShape<H>::WAVES, WideShape<H>::WAVES_PER_S
         finish(it - stride, par, y);
         par ^= 1;
 #pragma unroll
-        for (int v = 0; v < 8; ++v) y[v] = yn[v];
+        for (int v = 0; v < 4; ++v) y[v] = yn[v];
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
