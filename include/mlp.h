@@ -31,7 +31,18 @@
  *     every reduction runs in a fixed order and no floating-point atomics are
  *     used.
  *   - One context per stream; a context is not re-entrant and calls on it
- *     must not overlap.
+ *     must not overlap. Contexts of their own may be used from threads of
+ *     their own.
+ *   - Calls may be captured into a HIP graph; each replay does what the call
+ *     does, from the weights it finds.
+ *   - Data, sums and results are fp32. The large products are formed on the
+ *     bf16 matrix cores from operands split exactly into three bf16 parts, with
+ *     the error of plain fp32 products or less. Two limits of the split: an
+ *     operand that is infinite, or within 2^-8 of the largest fp32 value, gives
+ *     NaN where fp32 products might give an infinity; and parts below the
+ *     smallest bf16 value are lost, so operands under about 1e-33 in magnitude
+ *     count with fewer bits. Where a residual or an operand is not finite the
+ *     gradients may be NaN for more units than fp32 products would make so.
  */
 #ifndef MLP_H_
 #define MLP_H_
@@ -53,7 +64,7 @@ typedef enum {
     MLP_ERR_HIP = -4,          /* a HIP runtime call or kernel launch failed     */
     MLP_ERR_NONFINITE = -5,    /* a batch loss was NaN or infinite (diverged)    */
     MLP_ERR_INDEX = -6,        /* a kernel met a row index outside [0, n_rows)   */
-    MLP_ERR_TIMEOUT = -7       /* a wait inside the training kernel timed out    */
+    MLP_ERR_TIMEOUT = -7       /* a wait between running workgroups timed out    */
 } mlp_status;
 
 /* Largest mini-batch any call accepts. */
@@ -89,11 +100,18 @@ mlp_status mlp_set_stream(mlp_t ctx, void *stream);
  * mlp_train_epochs compute (never what: every strategy computes eqs. 11-19 on
  * the same rows). MLP_STRATEGY_FUSED is the default; the others exist for the
  * strategy comparison of the paper's Sec. VI.B (Table I).
- *   FUSED     all steps of a call in one kernel launch (the persistent
- *             trainer); batch sizes it has no launch plan for run on TILE
- *   TILE      per step, one fused kernel (each workgroup a slice of the batch:
- *             forward, backward and its partial gradients in registers) and
- *             one fixed-order reduction that applies the update; host loop
+ *   FUSED     mlp_train_epochs: all steps of a call in one kernel launch (the
+ *             persistent trainer, up to one workgroup per compute unit; if other
+ *             work keeps some of them from starting for two seconds, one of them
+ *             trains alone, slowly). Batches it has no launch plan for (more than
+ *             4,096 rows, 2,048 at hidden 1024), GPUs with too few compute units,
+ *             and calls of a few steps of more than 256 rows (512 at hidden 512,
+ *             1,024 at 1024; not at 256) run on TILE, and so do mlp_backward and
+ *             mlp_sgd_step
+ *   TILE      per step, one fused kernel (each workgroup a share of the batch:
+ *             forward, backward and its partial gradients in registers) and,
+ *             past 64 rows, one fixed-order reduction that applies the update;
+ *             host loop
  *   OPTIMIZED the paper's optimized strategy (Sec. V): LDS-tiled products on
  *             explicitly transposed operands, ReLU fused into the first
  *             product; one kernel per operation, intermediates in device
@@ -246,8 +264,10 @@ mlp_status mlp_train_epochs_static(int32_t hidden, float *W1, float *W2, const f
  * Conventions (device pointers, asynchronous stream semantics, host-side
  * argument checks that leave parameters untouched, sticky index errors,
  * bitwise reproducibility, one context per stream) are those of the calls
- * above. Each SGD step is a sequence of kernel launches from the host (MFMA
- * GEMMs over the batch's activations in the workspace). */
+ * above. Each SGD step is a sequence of kernel launches from the host: up to
+ * hidden 256, where that is the faster, a panel of rows through the whole net in
+ * one launch, the weight gradients in a second and the update in a third; else
+ * MFMA GEMMs over the batch's activations in the workspace. */
 typedef struct mlp_deep_ctx *mlp_deep_t;
 
 /* Parameters of a d_in-h-...-h-1 net with `layers` hidden layers:
@@ -257,9 +277,12 @@ int64_t mlp_deep_param_count(int32_t d_in, int32_t hidden, int32_t layers);
 
 /* Workspace bytes for batches up to max_batch (the activations of every layer
  * for max_batch rows, gradient partials, control words; up to hidden 256 also
- * the weights in matrix-core operand order); 0 if unsupported. The workspace
- * must be 256-byte aligned. mlp_deep_init also takes one without that last
- * part; calls then run as one launch per matrix product. */
+ * a last part for the panels: the weights in matrix-core operand order, 512
+ * partials of the output layer's gradient, and layers - 3 more buffers of
+ * max_batch x hidden floats, which for deep nets and large batches are most of
+ * it); 0 if unsupported. The workspace must be 256-byte aligned. mlp_deep_init
+ * also takes one without that last part; calls then run as one launch per
+ * matrix product. */
 size_t mlp_deep_workspace_bytes(int32_t d_in, int32_t hidden, int32_t layers, int64_t max_batch);
 
 /* Create a context bound to caller-owned parameters (updated in place by

@@ -222,7 +222,8 @@ static bool trains_on_trainer(const mlp_ctx *c, int64_t n, int64_t batch, int64_
 // A single gradient or step takes the tile path: the trainer's start (its
 // cooperative launch, registration and start barrier) outweighs the step (a step
 // of 64 rows at h = 256: 29 us on the trainer, 6.4 us on the tile path; of 4,096
-// rows 11 us). The trainer still serves it when a test hook names a shape.
+// rows 11 us). A test hook that names a shape (train_persistent.hip) puts it on the
+// trainer all the same: so the tests see the gradients of every shape.
 static bool single_on_trainer(const mlp_ctx *c, int64_t batch, TrainPlan *pl) {
     return train_shape_forced() && use_persistent(c, batch, pl);
 }

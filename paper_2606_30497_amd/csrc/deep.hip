@@ -35,7 +35,9 @@
 // (each a quarter, as 16 x 16 MFMA tiles), K in chunks of 32 staged in LDS,
 // alternating between two LDS buffers (one barrier per chunk); the next two
 // chunks' global loads are in flight while the current chunk is computed. Large
-// products of h >= 384 take 128 x 128 tiles of their own (gemm_block128). Two
+// products whose width is a multiple of 128 from 256 units up (at 256 only where the
+// panels of deep_panel.hip do not serve) take 128 x 128 tiles of their own
+// (gemm_block128). Two
 // flavours of the product:
 // - fp32: v_mfma_f32_16x16x4f32 on fp32 operands (in LDS, operands read along
 //   m or n stored k-major with a row stride of TM + 16 floats, operands read
@@ -1043,7 +1045,9 @@ static size_t deep_ws_bytes(int h, int L, int64_t mb) { return sizeof(float) * d
 // it would still leave fewer than four. The 64 x 64 tiles (the
 // MFMA-heavy products of wide layers) run the bf16x3 flavour, the narrower
 // ones (latency-bound, few chunks each) the fp32 one: bf16x3 made the 1024-wide
-// net 8 % faster and the 256-wide ones 3-6 % slower.
+// net 8 % faster and the 256-wide ones 3-6 % slower. (Steps and passes of nets up to
+// 256 units come here only where panel_pays sends them, or without the panels'
+// workspace.)
 static GemmArgs gemm_args(const float *A, int lda, const float *B, int ldb, float *C, int ldc,
                           int64_t c_split, int64_t M, int N, int64_t K, int splits, int64_t kc,
                           const float *G, int ldg, bool *small) {

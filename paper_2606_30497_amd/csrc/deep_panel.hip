@@ -159,10 +159,13 @@ struct PanelShape {
 
 // 16 RT rows. What bounds it: with 16 rows the weights' stream from L2 (h = 256,
 // L = 2: 836 KB a workgroup, about 50 bytes a clock into each CU, 7 us) and the
-// latency of the layers' epilogues and barriers; with 64 rows the matrix cores. At
-// 32-256x2-1 and 4,096 rows a step is 14.6 us of this, 9.9 of k_panel_wgrad and 4.6
-// of k_panel_apply, 27.0 us in a training run against 39.5 as GEMM launches; 1M rows
-// through 32-256x3-1 take 1.19 ms (235 TFLOP/s of fp32 work) against 6.9.
+// latency of the layers' epilogues and barriers; with 64 rows the matrix cores. A
+// step of 32-256x2-1 at 4,096 rows takes 27.0 us in a training run against 39.5 as
+// GEMM launches (under the profiler, which adds up to a microsecond a launch, 15.2 us
+// of this, 10.1 of k_panel_wgrad and 4.3 of k_panel_apply); 1M rows through 32-256x3-1
+// 1.20-1.26 ms, as the card's clock allows (221-232 TFLOP/s of fp32 work), against 6.9.
+// Panels of 64 rows in training spill 52 registers at 256 units and 20 at 192, and
+// remain the faster: 32-256x2-1 at 16,384 rows 72 us a step, 94 as GEMM launches.
 template <int H, int RT, bool TRAIN>
 __global__ __launch_bounds__((64 * PanelShape<H>::NW)) void k_panel(const PanelArgs a) {
     using S = PanelShape<H>;
@@ -783,6 +786,9 @@ void panel_carve(DeepCtx &c, float *p) {
 //   one layer: at most 64 rows (64 units 14.4 / 13.8; 14.0 / 16.0 at 256), and at 128
 //     units or more from 2,048 to 8,192 (256: 19.7 / 15.9 at 4,096; 26.0 / 28.3 at
 //     16,384).
+// (A training run's; single steps of more rows: two layers of 64 26.0 / 26.5 at 8,192
+// and 38.7 / 33.2 at 16,384; of 256 63.5 / 38.4, 94 / 72, and 333 / 232 at 65,536, where
+// three of 256 take 586 / 378 and eight of 192 1,170 / 716.)
 bool panel_pays(const DeepCtx &c, int64_t nb) {
     if (!c.frag) return false;
     const int h = c.hidden;

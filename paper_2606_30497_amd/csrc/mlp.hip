@@ -71,8 +71,9 @@ struct BatchItem {
 // a call is the latency of the gather, the weights' load and split, and two
 // launches; the matrix work of 20,001 rows at h = 256 is about 3 us of it. Against
 // the vector-ALU kernel it replaced (one unit a thread): the gradient of 20,001
-// gathered rows at h = 256 127 -> 14.2 us, training steps of 1,000 rows at h = 64
-// 39 -> 7.8 us and of 2,048 at h = 512 78 -> 12.2 us.
+// gathered rows at h = 256 128 -> 14.4 us, training steps of 1,000 rows at h = 64
+// 39 -> 7.2 us and of 2,048 at h = 512 78 -> 12.4 us. At 1024 units a wave holds eight
+// unit tiles and spills 52-57 registers: 32 rows take 13.2 us there, 7.2 at 512.
 template <int H, int WR, bool ONE>
 __global__ __launch_bounds__((BatchShape<H, WR>::NT)) void k_batch(
     const float *__restrict__ X, int64_t n_rows, const float *__restrict__ Y,
@@ -461,9 +462,10 @@ static hipError_t launch_batch(const Ctx &c, const float *X, int64_t n_rows, con
     return hipGetLastError();
 }
 
-// One workgroup runs up to this many rows itself (two passes of 32): 5.5-6.5 us a
-// step at h <= 256 against 8.0-8.6 us for 65 rows on three workgroups and the
-// reduction's launch (h = 1024, where a pass is longest: 18.5 against 17.7).
+// One workgroup runs up to this many rows itself (two passes of 32). Steps of 33 to 64
+// rows so, and on two workgroups with the reduction's launch: 5.0 us and 8.5 at
+// h <= 128, 6.4 and 8.7 at 256, 9.3 and 10.7 at 512. At 1024, where a pass is longest,
+// the two launches would be 4 % faster (17.7 us against 18.5); the line is one for all.
 constexpr int64_t ONE_ROWS = 64;
 
 // Workgroups of a batch of nb rows: one per pass of RB rows (64 at h = 32, else

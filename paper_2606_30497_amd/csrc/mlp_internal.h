@@ -62,7 +62,7 @@ struct TrainArgs {
     int64_t steps;            // steps to run in this call
     float lr;
     float inv_n;
-    int32_t mode;             // 0: SGD (update weights), 1: gradient only (one step)
+    int32_t mode;             // 0: SGD (update weights), 1: gradient only (one step; tests)
     int32_t hidden;
     int32_t epochs;
     float *W1, *W2;           // caller's weights (read at start, written at end)

@@ -406,8 +406,8 @@ struct Pos {
 //   s_memrealtime ticks (100 MHz) and [14] elapsed core cycles over the summed
 //   steps (their ratio is the clock), [15] 0.
 // Phases: 1 forward operands from LDS (waited for), 2 forward MFMAs, epilogue
-// and exchange-A stores, 3 exchange-A wait of row tile 0, 4 residual of tile 0
-// and exchange-A wait of tile 1, 5 residual of the last tile, the backward and
+// and exchange-A stores, 3 exchange-A wait (both row tiles at once), 4 residual of
+// tile 0 where there are two, 5 residual of the last tile, the backward and
 // the P partials into LDS, 6 P barrier, 7 exchange-B stores, 8 exchange-B wait
 // (owners), 9 update and exchange-C stores (owners), 10 owners barrier,
 // 11 exchange-C gather, 12 step barrier. A phase a wave does not run counts 0.
@@ -431,7 +431,8 @@ constexpr int START_GIVEN_UP = 1 << 30;
 // The whole call by one workgroup: where other work on the GPU keeps some of the
 // launch's workgroups from starting within the limit, the last of them to leave
 // trains alone. No other workgroup has touched the weights. Plain fp32, and few
-// registers rather than speed (it shares the kernel with the step loop): per batch the
+// registers rather than speed (it shares the kernel with the step loop; a step of 4,096
+// rows at h = 256 takes 3.4 ms, of 1,000 at h = 64 0.39): per batch the
 // residuals of all rows, a wave a row, into LDS (batches the trainer takes have at
 // most 4,096 rows); then a thread a unit sums the unit's gradient over the rows and
 // updates its column of W1, which no other unit's gradient reads.
@@ -813,13 +814,12 @@ __global__ __launch_bounds__(NTHR) void k_train(const TrainArgs a) {
                 asm volatile("" ::: "memory");
                 PHASE(2);
 
-                // ---- 2. exchange A, residual and backward, one row tile at a time --
+                // ---- 2. exchange A of all the wave's row tiles, then their residuals --
                 // lane (lq, li): rows 4 lq + 2 h, 4 lq + 2 h + 1 (h = li >> 3) of the
                 // tile from group peer li & 7; the group sums run as a symmetric
                 // butterfly over the 8 lanes of a half-row (a fixed order), and the
                 // other half-row supplies the lane's other two rows, so each lane
                 // ends with dZ2 of exactly the rows its backward MFMA operands need.
-                // The backward of a tile overlaps the exchange of the next.
                 const int hh = li >> 3;
                 const int peer = (li & 7) % PX;
                 W2 wa[RTW];
@@ -1367,9 +1367,9 @@ static TrainPlan plan_of(int inst) {
 // The instantiated shapes: (index, groups PX, workgroups per group PR, rows per
 // workgroup R, units per group U). hidden = PX * U; batches up to PR * R. Every
 // width has shapes up to 4,096 rows (1024: 2,048, whose 128 units a group leave no
-// LDS or mask bits for 128 rows): a step of 1,000 rows at h = 64 takes 3.8 us here
-// and 6.9 us in the tile path's two launches, of 2,048 rows at h = 512 5.0 against
-// 12.1, of 4,096 at h = 32, the closest, 4.9 against 7.7.
+// LDS or mask bits for 128 rows): a step of 1,000 rows at h = 64 takes 3.5 us here
+// and 7.2 us in the tile path's two launches, of 2,048 rows at h = 512 4.8 against
+// 12.4, of 4,096 at h = 32, the closest, 4.5 against 7.8.
 #define MLP_SHAPES(X)                                                   \
     X(0, 8, 32, 128, 32)   /* 32-256-1,  batch <= 4096 */             \
     X(1, 8, 32, 64, 32)    /* 32-256-1,  batch <= 2048 */             \
@@ -1417,8 +1417,10 @@ static const TrainPlan *all_plans(int *count) {
 
 // Test and diagnostic hooks, read from the environment (none skips work):
 //   MLP_PX=p, MLP_INST=i   restrict the choice to shapes with PX = p, or to
-//                          instance i (the parity tests run every instantiated
-//                          shape this way);
+//                          instance i, and put single steps and gradients on the
+//                          trainer too (the parity tests run every instantiated
+//                          shape this way, its gradients through mode 1 of the
+//                          kernel, which only they reach);
 //   MLP_START_TICKS=t      limit of the start barrier in 100 MHz ticks (0: every
 //                          launch is given up, and its last workgroup trains alone);
 //   MLP_FORCE_COHERENT=1   device-coherent exchange stores even when every group

@@ -305,8 +305,8 @@ def mlp_launch_info(ctx: Context, n, batch, epochs):
     return int(wg.value), int(launches.value)
 
 
-PHASE_NAMES = ("forward operands", "forward", "exchange A wait, tile 0",
-               "residual tile 0 + exchange A wait, tile 1", "residual + backward + P to LDS",
+PHASE_NAMES = ("forward operands", "forward", "exchange A wait",
+               "residual tile 0 (of two)", "residual + backward + P to LDS",
                "P barrier", "exchange B stores", "exchange B wait", "update + exchange C stores",
                "owners barrier", "exchange C gather", "step barrier")
 
