@@ -33,7 +33,8 @@
  *   - One context per stream; a context is not re-entrant and calls on it
  *     must not overlap. Contexts of their own may be used from threads of
  *     their own.
- *   - Calls may be captured into a HIP graph; each replay does what the call
+ *   - Forward, gradient, step and training calls may be captured into a HIP
+ *     graph (with no event timing enabled); each replay does what the call
  *     does, from the weights it finds.
  *   - Data, sums and results are fp32. The large products are formed on the
  *     bf16 matrix cores from operands split exactly into three bf16 parts, with
